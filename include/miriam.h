@@ -150,7 +150,8 @@ typedef struct miriam_op_info {
                                  across tiles the workgroups that fit the device at once; for the
                                  global->LDS pipelined contraction (paths 2 and 3) with one to two
                                  rounds of resident workgroups' worth of tiles, half the tiles (two
-                                 per workgroup) */
+                                 per workgroup); for its 256-pixel 3x3 variant the fewest workgroups
+                                 that keep the number of rounds */
 } miriam_op_info;
 
 /* Kernel family behind an op (diagnostic; results do not depend on it beyond rounding
@@ -159,7 +160,9 @@ typedef enum miriam_kernel_path {
     MIRIAM_PATH_OTHER = 0,       /* memory-bound operator kernels */
     MIRIAM_PATH_STAGED = 1,      /* contraction, operands staged through registers */
     MIRIAM_PATH_DMA = 2,         /* contraction, global->LDS pipeline, per-lane K decode */
-    MIRIAM_PATH_DMA_UNIFORM = 3, /* contraction, global->LDS pipeline, chunk-uniform filter taps */
+    MIRIAM_PATH_DMA_UNIFORM = 3, /* contraction, global->LDS pipeline, chunk-uniform filter taps; with
+                                    tile_m 256, the variant that keeps a 3x3 stride-1 tile's input
+                                    pixels in LDS for all nine taps */
     MIRIAM_PATH_SKINNY = 4,      /* small-batch fully connected, K split over logical waves */
     MIRIAM_PATH_HALO = 5,        /* direct 3x3 stride-1 convolution, input patch of the tile in LDS */
     MIRIAM_PATH_RESIDENT = 6     /* direct 3x3 stride-1 convolution, weights resident in registers

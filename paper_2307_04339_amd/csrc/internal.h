@@ -25,6 +25,9 @@ int igemm_kernels_bf16(int cfg, int lay, const void *out[3], int *lds);
 int igemm_mi_kernels_f32(int cfg, bool uni, const void *out[3], int *lds);
 int igemm_mi_kernels_f16(int cfg, bool uni, const void *out[3], int *lds);
 int igemm_mi_kernels_bf16(int cfg, bool uni, const void *out[3], int *lds);
+// 3x3 stride-1 patch kernel (fp16 / bf16): cfg CFG_PATCH_128 or CFG_PATCH_64
+int patch_kernels_f16(int cfg, const void *out[3], int *lds);
+int patch_kernels_bf16(int cfg, const void *out[3], int *lds);
 int pix_kernels(int dtype, int kind, bool vec, const void *out[3]);
 int row_kernels(int dtype, int kind, bool vec, const void *out[3]);
 int skinny_kernels(int dtype, int cg, const void *out[3]);  // cg: 16-column groups per tile (1 or 2)

@@ -73,7 +73,14 @@ struct IgemmArgs {
     int64_t mT, nT;        // tiles along m and n
     int64_t bdiv, sx0, sx1, sw0, sw1, sy0, sy1;  // batch offsets
     int64_t img_x;         // elements between images of x
-    int64_t tY, tX;        // direct 3x3 kernel: tile rows and tile columns per output image
+    union {
+        struct {
+            int64_t tY, tX;         // direct kernels: tile rows and tile columns per output image
+        };
+        struct {
+            FastDiv fd_pw, fd_ph;   // patch kernel: division by the padded row (Wo + 2) and image height (Ho + 2)
+        };
+    };
     FastDiv fd_howo, fd_wo; // division by Ho * Wo and by Wo (output pixel -> image, row, column)
     int32_t vec_store;     // 1: output / residual rows allow 16-byte vector access
     int32_t ksplit;        // K slices per output tile (1 = none); tile id = output tile * ksplit + slice
@@ -120,7 +127,11 @@ struct RowArgs {
 enum PixKind { PIX_DW = 0, PIX_MAX = 1, PIX_AVG = 2, PIX_EW = 3, PIX_DW3 = 4 };
 constexpr int kDwStrip = 4;  // PIX_DW3: output pixels along a row per lane item
 enum RowKind { ROW_SOFTMAX = 0, ROW_LAYERNORM = 1 };
-enum IgemmLayout { LAY_VEC = 0, LAY_SCALAR = 1, LAY_VEC_NB = 2, LAY_SCALAR_NB = 3, LAY_VEC_UNI = 4, LAY_HALO = 5, LAY_RW = 6 };
-enum IgemmCfg { CFG_32 = 1, CFG_64 = 2, CFG_128 = 3, CFG_128x64 = 4, CFG_256x128 = 6, CFG_HALO = 7, CFG_RW = 8 };
+enum IgemmLayout { LAY_VEC = 0, LAY_SCALAR = 1, LAY_VEC_NB = 2, LAY_SCALAR_NB = 3, LAY_VEC_UNI = 4, LAY_HALO = 5, LAY_RW = 6, LAY_PATCH = 7 };
+enum IgemmCfg { CFG_32 = 1, CFG_64 = 2, CFG_128 = 3, CFG_128x64 = 4, CFG_256x128 = 6, CFG_HALO = 7, CFG_RW = 8,
+                // library choice only (no descriptor code): 3x3 stride-1 patch kernel, 256 pixels x 128 / 64 channels
+                CFG_PATCH_128 = 101, CFG_PATCH_64 = 102, CFG_PATCH_64W = 103 };
+// patch kernel: padded-space pixels an LDS buffer holds (the W variant: wider images)
+constexpr int kPatchPixels = 512, kPatchPixelsW = 768;
 
 }  // namespace miriam

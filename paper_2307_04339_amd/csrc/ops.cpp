@@ -90,6 +90,10 @@ static void query_occupancy(miriam_op *op) {
     // as fit the device at once (one per tile when that is fewer)
     if (op->family == FAM_IGEMM && op->lay == LAY_RW && op->max_wg_per_cu[2] > 0)
         op->full_grid = std::min<int64_t>(op->T, (int64_t)device_cus() * op->max_wg_per_cu[2]);
+    // the patch kernel loads the next tile's first operands under the current tile's epilogue: as
+    // few workgroups as keep the number of rounds
+    if (op->family == FAM_IGEMM && op->lay == LAY_PATCH && op->max_wg_per_cu[2] > 0)
+        op->full_grid = cdiv(op->T, cdiv(op->T, (int64_t)device_cus() * op->max_wg_per_cu[2]));
     // the pipelined contraction with more tiles than resident workgroups, but at most twice as
     // many: half as many workgroups, two tiles each, none waiting for a second dispatch (VGG-16
     // b8 fp16, 128x128 tiles on 512 resident slots, cold caches: conv2_2's 784 tiles 50.8 ->
@@ -155,6 +159,54 @@ static int choose_cfg(int64_t batch, int64_t M, int64_t N, int64_t k_chunks) {
     if (batch * cdiv(M, 128) * cdiv(N, 64) >= fill) return CFG_128x64;
     if (batch * cdiv(M, 64) * cdiv(N, 64) >= fill) return CFG_64;
     return CFG_32;
+}
+
+static int patch_tile_n(int cfg) { return cfg == CFG_PATCH_128 ? 128 : 64; }
+
+// 3x3 stride-1 patch kernel (conv_patch.h) for fp16 / bf16 with C a multiple of 32, whole 16-byte
+// output pieces and 32-bit offsets: CFG_PATCH_*, or 0 where another kernel serves the layer.
+// *group: output pixels a tile stays within.  Lines measured back to back in a captured graph, fp16,
+// against the implicit GEMM (or the kernel named), us:
+//  - at least 3/8 of the CUs with a 256 x 64 tile: 96..104 tiles 8x56x56x64->64 9.4 -> 8.1,
+//    1x112x112x128->128 12.5 -> 10.4, 4x28x28x256->512 19.5 -> 15.3, 16x14x14x512->512 30.0 -> 25.7;
+//    50..56 tiles lose, 8x28x28x128->128 9.4 -> 10.0, 2x28x28x256->512 14.2 -> 14.7: a tile's K loop
+//    is then the whole time.  Where C is no multiple of 64 the implicit GEMM decodes K per lane, and
+//    3/16 suffice: 51 tiles 3x37x37x96->160 12.1 -> 8.6.
+//  - `narrow` (the resident-weight or the LDS-patch kernel would serve the layer): only up to one
+//    tile per CU.  16x56x56x64->64 (196 tiles) 13.6 -> 8.7, 8x90x90x64->64 (256) 18.9 -> 10.3;
+//    8x224x224x64->64 (1568) 41.9 -> 55.0, its weights streaming again for every tile.
+//  - 256 x 128 tiles beyond two rounds of 256 x 64 ones: 784 tiles 8x112x112x128->128 36.7 / 33.6
+//    (64 / 128 wide), 16x56x56x256->256 59.3 / 55.9; at two rounds, 8x56x56x256->256 30.4 / 30.0,
+//    the narrower tile keeps the finer tile space for shards.
+static int choose_patch(const miriam_op_desc &d, const IgemmArgs &a, bool vec, bool narrow, int64_t *group) {
+    const int64_t es = 2, lim = (int64_t)1 << 31;
+    if (d.kind != MIRIAM_OP_CONV2D || d.dtype == MIRIAM_F32 || d.kh != 3 || d.kw != 3 || d.stride != 1 || d.c % 32 != 0 ||
+        !vec || !a.vec_store || a.Nc % 8 != 0 || d.ksplit > 1)
+        return 0;
+    // 32-bit offsets into the operands, the output and the padded pixel space
+    if (d.n * a.img_x * es >= lim || ((a.Nc - 1) * a.ldw + a.K) * es >= lim || a.M * a.ldy * es >= lim ||
+        d.n * (a.Ho + 2) * (a.Wo + 2) >= lim - 2 * kPatchPixels)
+        return 0;
+    // the longest run of padded pixels under a tile of 256 output pixels, tiles across images or not
+    const int64_t pw = a.Wo + 2, howo = a.Ho * a.Wo;
+    auto lin = [&](int64_t m) { return (m / howo * (a.Ho + 2) + m % howo / a.Wo) * pw + m % a.Wo; };
+    auto longest = [&](int64_t pixels) {
+        int64_t most = 0;
+        for (int64_t m = 0; m < pixels && most <= kPatchPixelsW; m += 256) most = std::max(most, lin(std::min(m + 255, pixels - 1)) - lin(m));
+        return most + 2 * pw + 3;
+    };
+    int64_t run = longest(a.M);
+    *group = a.M;
+    if (run > kPatchPixels) {
+        run = longest(howo);
+        *group = howo;
+    }
+    if (run > kPatchPixelsW) return 0;
+    const int64_t cus = device_cus(), t64 = a.M / *group * cdiv(*group, 256) * cdiv(a.Nc, 64);
+    if (t64 * (d.c % 64 == 0 ? 8 : 16) < cus * 3) return 0;
+    if (narrow && t64 > cus) return 0;
+    if (run > kPatchPixels) return CFG_PATCH_64W;
+    return a.Nc > 64 && t64 > 2 * cus ? CFG_PATCH_128 : CFG_PATCH_64;
 }
 
 // ---------------------------------------------------------- device scratch
@@ -340,16 +392,37 @@ static int create_igemm(miriam_op *op) {
                        d.ksplit <= 1 && a.img_x * esize(d.dtype) < ((int64_t)1 << 31);
     const int64_t rw_T = d.n * halo_ty * halo_tx * cdiv(a.Nc, 64);
     int cfg = d.tile;
+    const bool wide_image = halo_tx * 32 * 4 <= a.Wo * 5;
+    const bool rw_fits = !memidx && rw_ok && rw_T >= (int64_t)device_cus() * 3 / 2 && wide_image;
+    const bool halo_fits = !memidx && halo_ok && a.Nc <= 64 && halo_T >= (int64_t)device_cus() * 3 / 2 && wide_image;
+    int64_t patch_group = 0;
+    const int patch = d.tile == 0 && !memidx ? choose_patch(d, a, a_vec && b_vec, rw_fits || halo_fits, &patch_group) : 0;
     // the memory-based index function is served by the pipelined kernel only
-    if (cfg == 0 && !memidx && rw_ok && rw_T >= (int64_t)device_cus() * 3 / 2 && halo_tx * 32 * 4 <= a.Wo * 5)
-        cfg = CFG_RW;
-    if (cfg == 0 && !memidx && halo_ok && a.Nc <= 64 && halo_T >= (int64_t)device_cus() * 3 / 2 &&
-        halo_tx * 32 * 4 <= a.Wo * 5)
-        cfg = CFG_HALO;
+    if (cfg == 0 && patch) cfg = patch;
+    if (cfg == 0 && rw_fits) cfg = CFG_RW;
+    if (cfg == 0 && halo_fits) cfg = CFG_HALO;
     if (cfg == 0) cfg = (skinny_ok && !memidx) ? TILE_SKINNY : choose_cfg(batch, a.M, a.Nc, cdiv(a.K * es, 128));
     if (memidx && (cfg == CFG_RW || cfg == CFG_HALO || cfg == TILE_SKINNY))
         return einval("memory-based index function: tiles 1..4 only (pipelined contraction kernel)");
-    if (cfg == CFG_RW) {
+    if (patch && cfg == patch) {
+        a.sx0 = patch_group;
+        a.mT = cdiv(patch_group, 256);
+        a.nT = cdiv(a.Nc, patch_tile_n(patch));
+        op->T = a.M / patch_group * a.mT * a.nT;
+        a.ksplit = 1;
+        a.cps = (int32_t)(d.c / 32);
+        a.fd_pw = make_fastdiv((uint32_t)(a.Wo + 2));
+        a.fd_ph = make_fastdiv((uint32_t)(a.Ho + 2));
+        a.x_bytes = (uint32_t)(d.n * a.img_x * es);
+        a.w_bytes = (uint32_t)(((a.Nc - 1) * a.ldw + a.K) * es);
+        a.y_bytes = (uint32_t)(a.M * a.ldy * es);
+        op->cfg = cfg;
+        op->tile_m = 256;
+        op->tile_n = patch_tile_n(patch);
+        op->lay = LAY_PATCH;
+        if ((d.dtype == MIRIAM_F16 ? patch_kernels_f16 : patch_kernels_bf16)(cfg, op->kern, &op->lds_bytes) != 0)
+            return einval("no patch kernel for this tile");
+    } else if (cfg == CFG_RW) {
         if (!rw_ok) return einval("tile 8 (resident-weight direct conv) needs an fp16/bf16 conv that is 3x3 stride 1 with C in {8,16,32,64} and at most 64 output channels, 3x3 stride 2 with C = 8 and at most 64 output channels, or 1x1 stride 1 pad 0 with C in {16,24,32,64}; 16-byte rows; images under 2 GiB; no split K");
         a.tX = halo_tx;
         a.tY = halo_ty;
@@ -812,7 +885,7 @@ int miriam_op_query(const miriam_op *op, miriam_op_info *out) {
     else if (op->family == FAM_IGEMM)
         out->path = op->lay == LAY_RW        ? MIRIAM_PATH_RESIDENT
                     : op->lay == LAY_HALO    ? MIRIAM_PATH_HALO
-                    : op->lay == LAY_VEC_UNI ? MIRIAM_PATH_DMA_UNIFORM
+                    : (op->lay == LAY_VEC_UNI || op->lay == LAY_PATCH) ? MIRIAM_PATH_DMA_UNIFORM
                     : op->lay == LAY_VEC     ? MIRIAM_PATH_DMA
                                              : MIRIAM_PATH_STAGED;
     else out->path = MIRIAM_PATH_OTHER;
