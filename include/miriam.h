@@ -159,7 +159,8 @@ typedef struct miriam_op_info {
 typedef enum miriam_kernel_path {
     MIRIAM_PATH_OTHER = 0,       /* memory-bound operator kernels */
     MIRIAM_PATH_STAGED = 1,      /* contraction, operands staged through registers */
-    MIRIAM_PATH_DMA = 2,         /* contraction, global->LDS pipeline, per-lane K decode */
+    MIRIAM_PATH_DMA = 2,         /* contraction, global->LDS pipeline, per-lane K decode (or mask of the
+                                    last K chunk) */
     MIRIAM_PATH_DMA_UNIFORM = 3, /* contraction, global->LDS pipeline, chunk-uniform filter taps; with
                                     tile_m 256, the variant that keeps a 3x3 stride-1 tile's input
                                     pixels in LDS for all nine taps */

@@ -291,16 +291,16 @@ __global__ __launch_bounds__(kWave * P, (P == 4 ? 2 : 1)) void halo_kernel(Igemm
                             const Vec16<T> rv = ld_vec(R + off);
 #pragma unroll
                             for (int e = 0; e < VEC; ++e)
-                                o.e[e] = TypeOps<T>::from_f(act_c<ACT>(cr[e] + TypeOps<T>::to_f(rv.e[e])));
+                                o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e] + TypeOps<T>::to_f(rv.e[e])));
                         } else {
 #pragma unroll
-                            for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_c<ACT>(cr[e]));
+                            for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e]));
                         }
                         st_vec(Y + off, o);
                     } else {
 #pragma unroll
                         for (int e = 0; e < VEC; ++e)
-                            if (n + e < a.Nc) st_f(Y + off + e, act_c<ACT>(RES ? cr[e] + ld_f(R + off + e) : cr[e]));
+                            if (n + e < a.Nc) st_f(Y + off + e, act_t<T, ACT>(RES ? cr[e] + ld_f(R + off + e) : cr[e]));
                     }
                 }
             };

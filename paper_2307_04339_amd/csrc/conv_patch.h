@@ -41,42 +41,9 @@
 // outer, tap (r, s) in row-major order, channel innermost.
 #pragma once
 
-#include <utility>
-
-#include "igemm_dma.h"
+#include "tile_regs.h"
 
 namespace miriam {
-
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// f(0), f(1), ..., f(N - 1) with compile-time indices (ActTag<i>).
-template <class F, int... I>
-__device__ __forceinline__ void static_for_(F &&f, std::integer_sequence<int, I...>) {
-    (f(ActTag<I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-    static_for_(f, std::make_integer_sequence<int, N>{});
-}
-
-// One 4-byte-per-lane buffer -> LDS load (lane i writes LDS bytes [lds + 4 i, + 4)), ordered like lds_dma16.
-__device__ __forceinline__ void buf_dma4(uint32_t voff, rsrc_t rsrc, uint32_t lds_addr) {
-    const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_addr);
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds"
-                 :
-                 : "v"(voff), "s"(rsrc), "s"(lds)
-                 : "memory", "m0");
-}
-
-// Wait until at most N vector-memory operations and no LDS reads of this wave are outstanding,
-// then meet the workgroup.
-template <int N>
-__device__ __forceinline__ void wait_and_meet() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
 
 template <class T, int TM, int TN, int WM, int P, int NPX>
 struct PatchKernel {
@@ -125,7 +92,6 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
     const rsrc_t rs_bias = make_rsrc(a.epi.bias, (uint32_t)a.epi.C * 4u), rs_bn = make_rsrc(a.epi.bn, (uint32_t)a.epi.C * 16u);
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(a.y, (short)0, (int)a.y_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.res), (short)0, (int)a.y_bytes, 0x00020000);
-    const bool has_res = (a.epi.flags & EPI_RES) != 0;
     const int64_t G = gridDim.x;
     const int64_t rank = wg_rank(blockIdx.x, G);
     const int64_t end = sh.begin + sh.len;
@@ -221,39 +187,13 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
     // two filter rows, and the head of the group that the first step completes (a third of chunk 1,
     // the third filter row)
     auto prologue = [&]() {
-        if (pw == 0 || P == 1) {
-#pragma unroll
-            for (int j = 0; j < TN / 64; ++j) {
-                const uint32_t v = (n0 + (uint32_t)(64 * j + lane)) * 4u;
-                if (a.epi.flags & EPI_BIAS) buf_dma4(v, rs_bias, lds0 + (uint32_t)(K_::RAW0 + 256 * j));
-                if (a.epi.flags & EPI_BN)
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        buf_dma4(v + (uint32_t)k * Nc32 * 4u, rs_bn, lds0 + (uint32_t)(K_::RAW0 + (k + 1) * TN * 4 + 256 * j));
-            }
-        }
+        if (pw == 0) load_channel_params<TN>(a.epi, rs_bias, rs_bn, n0, lane, lds0 + (uint32_t)K_::RAW0);
         issue_patch(rs_x, 0, 0, NPW);
         issue_w(0, 0);
         issue_w(0, 1);
 #pragma unroll
         for (int u = 0; u < HEAD; ++u) replace(1, 0, 2, u);
     };
-    // per-channel affine part (bias, batch norm) of the tile, from the raw parameters in LDS
-    auto make_affine = [&]() {
-        for (int c = tid; c < TN; c += K_::NT) {
-            const float *raw = reinterpret_cast<const float *>(smem_ + K_::RAW0) + c;
-            const float bias = (a.epi.flags & EPI_BIAS) ? raw[0] : 0.0f;
-            float sc = 1.0f, shf = bias;
-            if (a.epi.flags & EPI_BN) {
-                sc = raw[TN] / sqrtf(raw[4 * TN] + a.epi.eps);
-                shf = (bias - raw[3 * TN]) * sc + raw[2 * TN];
-            }
-            float *aff = reinterpret_cast<float *>(smem_ + K_::AFF0);
-            aff[c] = sc;
-            aff[TN + c] = shf;
-        }
-    };
-
     constexpr bool pipe = P == 4;  // next tile's first loads under the current epilogue
     int64_t t = sh.begin + rank;
     if (t >= end) return;
@@ -267,70 +207,11 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
         auto epilogue = [&](int rd, acc_t (&acc)[BP][BC]) {
             const int lam = rd * P + pw, wm = lam / WN, wn = lam % WN;
             trace_wave(sh, t, lam, pw, rd);
-            auto finish = [&](auto actc, auto resc) {
-                constexpr int ACT = decltype(actc)::value;
-                constexpr bool RES = decltype(resc)::value != 0;
-#pragma unroll
-                for (int c = 0; c < BC; ++c) {
-                    const int nl = wn * (TN / WN) + c * 32;
-                    const float *aff = reinterpret_cast<const float *>(smem + K_::AFF0) + nl + 4 * hx;
-                    f32x4 sc[4], shf[4];
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        sc[g] = *reinterpret_cast<const f32x4 *>(aff + 8 * g);
-                        shf[g] = *reinterpret_cast<const f32x4 *>(aff + TN + 8 * g);
-                    }
-#pragma unroll
-                    for (int b = 0; b < BP; ++b) {
-                        const uint32_t m = tm0 + (uint32_t)(wm * (TM / WM) + b * 32 + xl);
-                        const uint32_t row = m * (uint32_t)a.ldy;
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {  // channels 16 h .. 16 h + 15 of the block
-                            const uint32_t n = tn0 + (uint32_t)(nl + 16 * h + 8 * hx);
-                            const uint32_t off = (m <= tlast) & (n < Nc32) ? (row + n) * 2u : kOutOfRange;
-                            uint32_t lo[2], hi[2];  // packed quarters 2h and 2h + 1 (4 channels each)
-                            uint32_t rlo[2] = {0u, 0u}, rhi[2] = {0u, 0u};
-                            if constexpr (RES) {
-                                const u32x4 rv = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off, 0, 0));
-#pragma unroll
-                                for (int k = 0; k < 2; ++k) {
-                                    const auto sw = __builtin_amdgcn_permlane32_swap(rv[k], rv[2 + k], false, false);
-                                    rlo[k] = sw[0];
-                                    rhi[k] = sw[1];
-                                }
-                            }
-                            auto quarter = [&](int g, uint32_t *r, uint32_t *o) {
-#pragma unroll
-                                for (int k = 0; k < 2; ++k) {
-                                    f32x2 e;
-#pragma unroll
-                                    for (int u = 0; u < 2; ++u) {
-                                        float v = acc[b][c][4 * g + 2 * k + u] * sc[g][2 * k + u] + shf[g][2 * k + u];
-                                        if constexpr (RES)
-                                            v += TypeOps<T>::to_f(__builtin_bit_cast(T, (uint16_t)(u ? r[k] >> 16 : r[k] & 0xffffu)));
-                                        e[u] = act_c<ACT>(v);
-                                    }
-                                    typedef T t2 __attribute__((ext_vector_type(2)));
-                                    o[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(e, t2));
-                                }
-                            };
-                            quarter(2 * h, rlo, lo);
-                            quarter(2 * h + 1, rhi, hi);
-                            // lanes 0..31 keep channels 16 h .. + 7, lanes 32..63 take 16 h + 8 .. + 15
-                            u32x4 o;
-#pragma unroll
-                            for (int k = 0; k < 2; ++k) {
-                                const auto sw = __builtin_amdgcn_permlane32_swap(lo[k], hi[k], false, false);
-                                o[k] = sw[0];
-                                o[2 + k] = sw[1];
-                            }
-                            __builtin_amdgcn_raw_buffer_store_b128(o, ry, (int)off, 0, 0);
-                        }
-                    }
-                }
-            };
-            if (has_res) with_act(a.epi.act, [&](auto actc) { finish(actc, ActTag<1>{}); });
-            else with_act(a.epi.act, [&](auto actc) { finish(actc, ActTag<0>{}); });
+            finish_tile<T>(a.epi, smem + K_::AFF0, TN, wn * (TN / WN), tn0, Nc32, ry, rr, acc, [&](int b, int x, uint32_t &row) {
+                const uint32_t m = tm0 + (uint32_t)(wm * (TM / WM) + b * 32 + x);
+                row = m * (uint32_t)a.ldy;
+                return m <= tlast;
+            });
         };
 
 #pragma unroll 1
@@ -379,7 +260,7 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
 #pragma unroll
             for (int b = 0; b < BP; ++b) address1(b, 0, tap_offset(0, 0, 0u));
             static_for<NOP>([&](auto i) { fetch1(decltype(i)::value, 0, 0, 0, 0); });
-            if (rd == 0) make_affine();
+            if (rd == 0) make_affine(a.epi, smem_ + K_::RAW0, smem_ + K_::AFF0, TN, tid, K_::NT);
             __builtin_amdgcn_sched_barrier(0);
             for (int cc = 0; cc < CC; ++cc) {
                 const uint32_t pb = (uint32_t)((cc & 1) * K_::PATCH);

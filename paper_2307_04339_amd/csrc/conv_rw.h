@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P, KS, ST>::WAVES_PER_SI
                             const int dx = (e / 4) * 8 + (e % 4);
                             const float v = acc[sl][i][e] * esc[rd] + esh[rd];
                             if constexpr (ACT < 0) cb[dx * LDC] = v;
-                            else yb[dx * LDY] = TypeOps<T>::from_f(act_c<ACT>(v));
+                            else yb[dx * LDY] = TypeOps<T>::from_f(act_t<T, ACT>(v));
                         }
                     }
                 }
@@ -356,12 +356,12 @@ __global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P, KS, ST>::WAVES_PER_SI
                     const Vec16<T> rv = ld_vec(R + off);
                     Vec16<T> o;
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_c<ACT>(cr[e] + TypeOps<T>::to_f(rv.e[e])));
+                    for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e] + TypeOps<T>::to_f(rv.e[e])));
                     st_vec(Y + off, o);
                 } else {
 #pragma unroll
                     for (int e = 0; e < VEC; ++e)
-                        if (n + e < a.Nc) st_f(Y + off + e, act_c<ACT>(cr[e] + ld_f(R + off + e)));
+                        if (n + e < a.Nc) st_f(Y + off + e, act_t<T, ACT>(cr[e] + ld_f(R + off + e)));
                 }
             }
         };

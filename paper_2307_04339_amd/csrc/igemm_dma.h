@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kWave * P, (DmaKernel<T, TM, TN, MS, P>::WAVES_PER_
                         // replaced by an offset past the buffer, so the store is dropped)
                         Vec16<T> o;
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_c<ACT>(cr[e]));
+                        for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e]));
                         const uint32_t off = ((uint32_t)yoff + (uint32_t)m * (uint32_t)a.ldy + (uint32_t)n) * (uint32_t)sizeof(T);
                         __builtin_amdgcn_raw_buffer_store_b128(o.u, ry, (int)(m < a.M && n < a.Nc ? off : kOutOfRange), 0, 0);
                         continue;
@@ -322,16 +322,16 @@ __global__ __launch_bounds__(kWave * P, (DmaKernel<T, TM, TN, MS, P>::WAVES_PER_
                             const Vec16<T> rv = ld_vec(R + off);
 #pragma unroll
                             for (int e = 0; e < VEC; ++e)
-                                o.e[e] = TypeOps<T>::from_f(act_c<ACT>(cr[e] + TypeOps<T>::to_f(rv.e[e])));
+                                o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e] + TypeOps<T>::to_f(rv.e[e])));
                         } else {
 #pragma unroll
-                            for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_c<ACT>(cr[e]));
+                            for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e]));
                         }
                         st_vec(Y + off, o);
                     } else {
 #pragma unroll
                         for (int e = 0; e < VEC; ++e)
-                            if (n + e < a.Nc) st_f(Y + off + e, act_c<ACT>(RES ? cr[e] + ld_f(R + off + e) : cr[e]));
+                            if (n + e < a.Nc) st_f(Y + off + e, act_t<T, ACT>(RES ? cr[e] + ld_f(R + off + e) : cr[e]));
                     }
                 }
             };

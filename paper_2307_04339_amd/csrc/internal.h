@@ -25,6 +25,11 @@ int igemm_kernels_bf16(int cfg, int lay, const void *out[3], int *lds);
 int igemm_mi_kernels_f32(int cfg, bool uni, const void *out[3], int *lds);
 int igemm_mi_kernels_f16(int cfg, bool uni, const void *out[3], int *lds);
 int igemm_mi_kernels_bf16(int cfg, bool uni, const void *out[3], int *lds);
+// register-tile pipelined contraction: cfg CFG_PIPE_*; filters of several taps, or one tap
+int pipe_kernels_taps_f16(int cfg, const void *out[3], int *lds);
+int pipe_kernels_taps_bf16(int cfg, const void *out[3], int *lds);
+int pipe_kernels_one_f16(int cfg, const void *out[3], int *lds);
+int pipe_kernels_one_bf16(int cfg, const void *out[3], int *lds);
 // 3x3 stride-1 patch kernel (fp16 / bf16): cfg CFG_PATCH_128 or CFG_PATCH_64
 int patch_kernels_f16(int cfg, const void *out[3], int *lds);
 int patch_kernels_bf16(int cfg, const void *out[3], int *lds);

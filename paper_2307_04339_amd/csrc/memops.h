@@ -94,7 +94,7 @@ __device__ __forceinline__ void pix_item(const PixArgs &a, int64_t u) {
         for (int e = 0; e < V; ++e) {
             float v = epilogue_pre(a.epi, cp[e], TypeOps<T>::to_f(xv[e]));
             if (a.epi.flags & EPI_RES) v += TypeOps<T>::to_f(rv[e]);
-            acc[e] = act_c<ACT>(v);
+            acc[e] = act_t<T, ACT>(v);
         }
     } else {
         const uint32_t HoWo = (uint32_t)(a.Ho * a.Wo), Wo = (uint32_t)a.Wo;
@@ -159,7 +159,7 @@ __device__ __forceinline__ void pix_item(const PixArgs &a, int64_t u) {
             for (int e = 0; e < V; ++e) {
                 float v = epilogue_pre(a.epi, cp[e], acc[e]);
                 if (a.epi.flags & EPI_RES) v += TypeOps<T>::to_f(rv[e]);
-                acc[e] = act_c<ACT>(v);
+                acc[e] = act_t<T, ACT>(v);
             }
         }
     }
@@ -261,7 +261,7 @@ __device__ __forceinline__ void pix_dw3_item(const PixArgs &a, int64_t u) {
         for (int e = 0; e < V; ++e) {
             float v = epilogue_pre(a.epi, cp[e], acc[i][e]);
             if (a.epi.flags & EPI_RES) v += TypeOps<T>::to_f(rv[e]);
-            ov[e] = act_c<ACT>(v);
+            ov[e] = act_t<T, ACT>(v);
         }
         T *dst = Y + pix * a.C + c0;
         Vec16<T> o;

@@ -1,0 +1,123 @@
+"""GPU parity and elastic invariance of the register-tile pipelined contraction at the edges of its
+tiles (rows, columns, K chunks, batches, filter taps), through the library's own choice of tile."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import bits, empty, f32_dev, gpu_available, rand, rel_err, to_f64
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs an MI355X")]
+
+# one rounding to the output type (half an ulp: 2^-11 and 2^-8 of the value) plus fp32 sums of at
+# most a few thousand products (below 1e-4 of the rms here) and, for GELU, an erf of 1.5e-7
+TOL = {"f16": 2.0 ** -11 + 1e-4, "bf16": 2.0 ** -8 + 1e-4}
+
+
+@pytest.fixture(scope="module")
+def ops():
+    from paper_2307_04339_amd import ops as o
+    return o
+
+
+def _is_pipe(op, tile):
+    # no other kernel of this path has these LDS sizes: two or more stages plus 28 bytes per column
+    from paper_2307_04339_amd import _lib as L
+    tm, tn = tile
+    return (op.info.path in (L.PATH_DMA, L.PATH_DMA_UNIFORM)
+            and (op.info.tile_m, op.info.tile_n, op.info.ksplit) == (tm, tn, 1)
+            and (op.info.lds_bytes - 28 * tn) % ((tm + tn) * 128) == 0)
+
+
+def _elastic(op, y, orc):
+    ref = bits(y)
+    for n, block in [(1, 256), (3, 256), (2, 128), (5, 64)]:
+        y.fill_(float("nan"))
+        for j, (b, l) in enumerate(reversed(orc.balanced_split(op.T, n))):
+            op.launch(b, l, [l, 7, l + 3][j % 3], block)
+        torch.cuda.synchronize()
+        assert bits(y) == ref, (n, block)
+
+
+# M, N, K, act, residual, row strides padded by 8, tile
+GEMMS = [
+    (500, 520, 200, "gelu", True, True, (64, 64)),       # K tail of 8, last column tile 8 wide
+    (1027, 264, 40, "none", False, False, (64, 64)),     # a single partial chunk
+    (2000, 520, 72, "relu", False, True, (128, 64)),
+    (2000, 1032, 136, "relu6", True, False, (128, 128)),
+    (4104, 1032, 64, "none", False, False, (256, 128)),
+    (4000, 3064, 128, "gelu", False, False, (256, 192)),
+]
+
+
+@pytest.mark.parametrize("case", GEMMS)
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_pipe_gemm_matches_oracle_and_is_elastic(ops, orc, dtype, case):
+    M, N, K, act, has_res, padded, tile = case
+    ld = K + 8 if padded else K
+    x, x64 = rand((M, ld), dtype, seed=1)
+    w, w64 = rand((N, ld), dtype, seed=2, lo=-0.2, hi=0.2)
+    x[:, K:] = float("nan")  # past the row's K values: never used
+    w[:, K:] = float("nan")
+    b64 = np.random.default_rng(3).uniform(-1, 1, N).astype(np.float32).astype(np.float64)
+    res, r64 = rand((M, N), dtype, seed=4) if has_res else (None, None)
+    y = empty((M, N), dtype)
+    op = ops.gemm(x, w, y, bias=f32_dev(b64), residual=res, act=act, ldx=ld, ldw=ld, k=K)
+    assert _is_pipe(op, tile), (op.info.path, op.info.tile_m, op.info.tile_n, op.info.lds_bytes)
+    op.run()
+    torch.cuda.synchronize()
+    ref = orc.linear(np.ascontiguousarray(x64[:, :K]), np.ascontiguousarray(w64[:, :K]), bias=b64, residual=r64, act=act)
+    err = rel_err(to_f64(y), ref)
+    print(f"pipe {dtype} {case}: T={op.T} rel={err:.3e}")
+    assert err <= TOL[dtype], err
+    _elastic(op, y, orc)
+
+
+# N, H, W, C, K, ks, stride, pad, act, bn, residual, tile
+CONVS = [
+    (2, 40, 40, 64, 264, 3, 2, 1, "relu", True, False, (64, 64)),
+    (9, 21, 23, 144, 24, 1, 1, 0, "none", True, True, (64, 64)),     # one tap, K tail of 16, narrow output
+    (9, 41, 23, 40, 72, 1, 2, 0, "relu6", False, False, (64, 64)),   # one tap, stride 2, K below a chunk
+    (15, 40, 40, 64, 136, 3, 2, 1, "relu", False, True, (128, 64)),
+    (15, 40, 40, 64, 392, 2, 2, 0, "none", True, False, (128, 128)),
+    (15, 40, 40, 64, 776, 2, 2, 0, "relu", False, False, (256, 128)),
+]
+
+
+@pytest.mark.parametrize("case", CONVS)
+def test_pipe_conv_matches_oracle_and_is_elastic(ops, orc, case):
+    N, H, W, C, K, ks, st, pad, act, has_bn, has_res, tile = case
+    dtype = "bf16" if has_bn else "f16"
+    x, x64 = rand((N, H, W, C), dtype, seed=1)
+    w, w64 = rand((K, ks, ks, C), dtype, seed=2, lo=-0.2, hi=0.2)
+    Ho, Wo = (H + 2 * pad - ks) // st + 1, (W + 2 * pad - ks) // st + 1
+    rng = np.random.default_rng(3)
+    bn64 = np.stack([rng.uniform(0.8, 1.2, K), rng.uniform(-0.1, 0.1, K), rng.uniform(-0.1, 0.1, K),
+                     rng.uniform(0.8, 1.2, K)]).astype(np.float32).astype(np.float64) if has_bn else None
+    res, r64 = rand((N, Ho, Wo, K), dtype, seed=4) if has_res else (None, None)
+    y = empty((N, Ho, Wo, K), dtype)
+    op = ops.conv2d(x, w, y, stride=st, pad=pad, bn=f32_dev(bn64) if has_bn else None, residual=res, act=act)
+    assert _is_pipe(op, tile), (op.info.path, op.info.tile_m, op.info.tile_n, op.info.lds_bytes)
+    op.run()
+    torch.cuda.synchronize()
+    ref = orc.conv2d(x64, w64, stride=st, pad=pad, bn=None if bn64 is None else tuple(bn64), residual=r64, act=act)
+    err = rel_err(to_f64(y), ref)
+    print(f"pipe {dtype} {case}: T={op.T} rel={err:.3e}")
+    assert err <= TOL[dtype], err
+    _elastic(op, y, orc)
+
+
+@pytest.mark.parametrize("B,H,S,tile", [(4, 6, 136, (64, 64)), (2, 12, 264, (128, 128)), (3, 12, 264, (256, 128))])
+def test_pipe_batched_scores_match_oracle(ops, orc, B, H, S, tile):
+    D = 64
+    qkv, q64 = rand((B * S, 3 * H * D), "bf16", seed=5)
+    y = empty((B * H, S, S), "bf16")
+    op = ops.bgemm(qkv, qkv[:, H * D:], y, m=S, n=S, k=D, batch=B * H, batch_div=H, ldx=3 * H * D, ldw=3 * H * D, ldy=S,
+                   sx=(S * 3 * H * D, D), sw=(S * 3 * H * D, D), sy=(H * S * S, S * S))
+    assert _is_pipe(op, tile), (op.info.path, op.info.tile_m, op.info.tile_n, op.info.lds_bytes)
+    op.run()
+    torch.cuda.synchronize()
+    q = q64.reshape(B, S, 3, H, D)
+    ref = np.einsum("bihd,bjhd->bhij", q[:, :, 0], q[:, :, 1]).reshape(B * H, S, S)
+    assert rel_err(to_f64(y), ref) <= TOL["bf16"]
+    _elastic(op, y, orc)
