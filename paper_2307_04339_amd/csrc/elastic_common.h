@@ -97,6 +97,19 @@ template <class T> __device__ __forceinline__ Vec16<T> zero_vec() {
     return v;
 }
 
+// 16 bytes at an address that is only a multiple of the element's (4 bytes for N floats).
+struct __attribute__((packed, aligned(2))) Loose16 { u32x4 u; };
+struct __attribute__((packed, aligned(4))) Loose16f { f32x4 f; };
+
+template <class T> __device__ __forceinline__ Vec16<T> ld_loose(const T *p) {
+    Vec16<T> v;
+    v.u = reinterpret_cast<const Loose16 *>(p)->u;
+    return v;
+}
+template <class T> __device__ __forceinline__ void st_loose(T *p, const Vec16<T> &v) {
+    reinterpret_cast<Loose16 *>(p)->u = v.u;
+}
+
 // ------------------------------------------------------------- epilogue
 __device__ __forceinline__ float gelu_erf(float v) {
     return 0.5f * v * (1.0f + erff(v * 0.70710678118654752440f));

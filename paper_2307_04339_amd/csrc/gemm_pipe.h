@@ -64,7 +64,10 @@ struct PipeKernel {
 };
 
 // TAPS: filters of more than one tap; without, one tap (products, 1x1 convolutions) and any K.
-template <class T, int TM, int TN, int WM, int P, bool TAPS>
+// NB: right operand stored [k][n] (attention's values).  A chunk's 64 k rows of 64 columns are staged
+// as they lie, 128 bytes each with the halves of rows 2 and 3 of every four swapped, and
+// ds_read_b64_tr_b16 turns four rows into four K values per lane, two reads per operand.
+template <class T, int TM, int TN, int WM, int P, bool TAPS, bool NB>
 __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>::STAGE < 24 * 1024 ? 2 : 1)) void pipe_kernel(IgemmArgs a, Shard sh) {
     typedef PipeKernel<T, TM, TN, WM, P> K_;
     typedef typename K_::MF MF;
@@ -72,6 +75,7 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
     constexpr int WN = K_::WN, BP = K_::BP, BC = K_::BC, NIA = K_::NIA, NIB = K_::NIB, NL = K_::NL, NK = K_::NK, LA = K_::LA;
     constexpr int NS = K_::NS, S = K_::S, NM = K_::NM, NOP = K_::NOP, HEAD = K_::HEAD, PRE = K_::PRE, AHEAD = K_::AHEAD, MPK = K_::MPK;
     constexpr int ROUNDS = K_::ROUNDS, NST = K_::NST, ES = K_::ES, KT = K_::KT, VEC = 16 / ES;
+    static_assert(!NB || (ES == 2 && TN == 64 && !TAPS), "[k][n] operands: 16-bit, 64 columns, one tap");
     constexpr bool PIPE = P == 4 && LA == 1;  // next tile's first loads under the current epilogue
 
     __shared__ __attribute__((aligned(1024))) char smem_[K_::LDS_BYTES];
@@ -131,8 +135,13 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
         static_for<NIB>([&](auto j_) {
             constexpr int j = decltype(j_)::value;
             const int q = j * P + pw;
-            const uint32_t n = n0 + (uint32_t)(8 * q + lrow);
-            voff_b[j] = n < Nc32 ? (n * (uint32_t)a.ldw + swz(q)) * (uint32_t)ES : kOutOfRange;
+            if constexpr (NB) {
+                const uint32_t n = n0 + (uint32_t)(((lane & 7) ^ ((lrow << 1) & 4)) * VEC);
+                voff_b[j] = n < Nc32 ? ((uint32_t)(8 * q + lrow) * (uint32_t)a.ldw + n) * (uint32_t)ES : kOutOfRange;
+            } else {
+                const uint32_t n = n0 + (uint32_t)(8 * q + lrow);
+                voff_b[j] = n < Nc32 ? (n * (uint32_t)a.ldw + swz(q)) * (uint32_t)ES : kOutOfRange;
+            }
         });
         static_for<NIA>([&](auto j_) {
             constexpr int j = decltype(j_)::value;
@@ -170,14 +179,15 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
             });
             static_for<NIB>([&](auto j_) {
                 constexpr int j = decltype(j_)::value;
-                voff_b[j] = uc + (int32_t)swz(j * P + pw) < C32 ? voff_b[j] : kOutOfRange;
+                const int32_t k = NB ? 8 * (j * P + pw) + lrow : (int32_t)swz(j * P + pw);
+                voff_b[j] = uc + k < C32 ? voff_b[j] : kOutOfRange;
             });
         }
     };
     // on to the next chunk
     auto advance = [&]() __attribute__((always_inline)) {
         ++lch;
-        kb += 128u;
+        kb += NB ? (uint32_t)(KT * ES) * (uint32_t)a.ldw : 128u;
         uc += KT;
         if constexpr (TAPS) {
             if (uc == C32) {
@@ -237,8 +247,28 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
             const uint32_t sw = (uint32_t)(hx ^ ((xl >> 1) & 7)) << 4;
             const uint32_t abase = (uint32_t)(wm * (TM / WM) + xl) * 128u + sw;
             const uint32_t bbase = (uint32_t)(TM + wn * (TN / WN) + xl) * 128u + sw;
+            // NB: lane l of a group of 16 reads 8 bytes of k row (l & 15) / 4 (+ 8 for the upper half), at
+            // column 4 (l & 3) of its group's 16; column block i flips bit 6 together with the row swizzle
+            const uint32_t nbase = (uint32_t)(TM * 128) + (uint32_t)(8 * hx + ((lane >> 2) & 3)) * 128u +
+                                   ((uint32_t)((((lane >> 3) & 1) << 2) ^ (wn * (TN / WN) / 8) ^ (((lane >> 3) & 2) | ((lane >> 1) & 1))) << 4) +
+                                   (uint32_t)(lane & 1) * 8u;
             // operand i (column blocks, then row blocks) of k-step kk of the stage at byte st
             auto fetch1 = [&](int i, int kk, uint32_t st, int set) __attribute__((always_inline)) {
+                if constexpr (NB) {
+                    if (i < BC) {
+                        typedef short s16x4 __attribute__((ext_vector_type(4)));
+                        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                        const uint32_t at = lds0 + (nbase ^ (uint32_t)(i << 6)) + st + (uint32_t)(kk * 2048);
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) {
+                            const u32x2 v = __builtin_bit_cast(
+                                u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(at + (uint32_t)(r * 512))));
+                            wo[set][i][2 * r] = v[0];
+                            wo[set][i][2 * r + 1] = v[1];
+                        }
+                        return;
+                    }
+                }
                 if (i < BC) wo[set][i] = *reinterpret_cast<const u32x4 *>(smem + ((bbase ^ (uint32_t)(kk << 5)) + st + i * 4096));
                 else xo[set][i - BC] = *reinterpret_cast<const u32x4 *>(smem + ((abase ^ (uint32_t)(kk << 5)) + st + (i - BC) * 4096));
             };
@@ -321,12 +351,23 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
     wait_vmcnt<0>();  // no load into LDS outlives the workgroup
 }
 
-template <class T, int TM, int TN, int WM, bool TAPS>
+template <class T, int TM, int TN, int WM, bool TAPS, bool NB = false>
 inline void pipe_table(const void *out[3], int *lds) {
-    out[0] = reinterpret_cast<const void *>(&pipe_kernel<T, TM, TN, WM, 1, TAPS>);
-    out[1] = reinterpret_cast<const void *>(&pipe_kernel<T, TM, TN, WM, 2, TAPS>);
-    out[2] = reinterpret_cast<const void *>(&pipe_kernel<T, TM, TN, WM, 4, TAPS>);
+    out[0] = reinterpret_cast<const void *>(&pipe_kernel<T, TM, TN, WM, 1, TAPS, NB>);
+    out[1] = reinterpret_cast<const void *>(&pipe_kernel<T, TM, TN, WM, 2, TAPS, NB>);
+    out[2] = reinterpret_cast<const void *>(&pipe_kernel<T, TM, TN, WM, 4, TAPS, NB>);
     *lds = PipeKernel<T, TM, TN, WM, 4>::LDS_BYTES;
+}
+
+// Right operand stored [k][n].
+template <class T>
+inline int pipe_nb_table_cfg(int cfg, const void *out[3], int *lds) {
+    switch (cfg) {
+    case CFG_PIPE_64: pipe_table<T, 64, 64, 2, false, true>(out, lds); return 0;
+    case CFG_PIPE_128x64: pipe_table<T, 128, 64, 4, false, true>(out, lds); return 0;
+    case CFG_PIPE_256x64: pipe_table<T, 256, 64, 4, false, true>(out, lds); return 0;
+    default: return -1;
+    }
 }
 
 template <class T, bool TAPS>

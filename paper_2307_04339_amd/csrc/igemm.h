@@ -91,8 +91,8 @@ struct IgemmKernel {
     static constexpr int SL = LW < MAXSL ? LW : MAXSL;   // logical waves held at once
     static constexpr int ROUNDS = LW / SL;               // sequential passes over K
     static constexpr bool A_VEC = (LAY == LAY_VEC || LAY == LAY_VEC_NB);
-    static constexpr bool B_NMAJ = (LAY == LAY_VEC_NB || LAY == LAY_SCALAR_NB);
-    static constexpr bool B_VEC = (LAY == LAY_VEC || LAY == LAY_VEC_NB);
+    static constexpr bool B_NMAJ = (LAY == LAY_VEC_NB || LAY == LAY_SCALAR_NB || LAY == LAY_RAG_NB);
+    static constexpr bool B_VEC = (LAY == LAY_VEC || LAY == LAY_VEC_NB || LAY == LAY_RAG_NB);
     static constexpr int NVA = (TM * KPR + NT - 1) / NT;           // A vectors per thread
     static constexpr int NVB = (TN * KPR + NT - 1) / NT;           // B vectors per thread
     static constexpr int LDC = TN + 4;                   // staged output row (fp32)
@@ -203,6 +203,20 @@ __global__ __launch_bounds__(kWave * P) void igemm_kernel(IgemmArgs a, Shard sh)
                         const int32_t h = a_h0[j] + kr, w = a_w0[j] + ks;
                         const bool ok = a_ok[j] && kr < KH32 && h >= 0 && h < a.H && w >= 0 && w < a.W;
                         ra[j] = ok ? ld_vec(Xb + a_img[j] + ((int64_t)h * a.W + w) * a.ldx + kc) : zero_vec<T>();
+                    } else if constexpr (LAY == LAY_RAG_NB) {
+                        // rows of one tap at any alignment: whole pieces in one load, the last by element
+                        Vec16<T> v = zero_vec<T>();
+                        if (a_ok[j] && kr == 0) {
+                            const T *p = Xb + a_img[j] + kc;
+                            if (kc + VEC <= C32) {
+                                v = ld_loose(p);
+                            } else {
+#pragma unroll
+                                for (int e = 0; e < VEC; ++e)
+                                    if (kc + e < C32) v.e[e] = p[e];
+                            }
+                        }
+                        ra[j] = v;
                     } else {
                         // element loads; (r, s, c) stepped incrementally from the slot's first element
                         Vec16<T> v = zero_vec<T>();
@@ -364,10 +378,10 @@ __global__ __launch_bounds__(kWave * P) void igemm_kernel(IgemmArgs a, Shard sh)
                     if (m >= a.M) continue;
                     const float *cr = Cs + row * LDC + col;
                     const int64_t off = yoff + m * a.ldy + n;
-                    if (a.vec_store && n + VEC <= a.Nc) {
+                    if (n + VEC <= a.Nc) {  // whole pieces; rows at any element (a.vec_store: 16 bytes)
                         Vec16<T> o;
                         if constexpr (RES) {
-                            const Vec16<T> rv = ld_vec(R + off);
+                            const Vec16<T> rv = ld_loose(R + off);
 #pragma unroll
                             for (int e = 0; e < VEC; ++e)
                                 o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e] + TypeOps<T>::to_f(rv.e[e])));
@@ -375,7 +389,7 @@ __global__ __launch_bounds__(kWave * P) void igemm_kernel(IgemmArgs a, Shard sh)
 #pragma unroll
                             for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e]));
                         }
-                        st_vec(Y + off, o);
+                        st_loose(Y + off, o);
                     } else {
 #pragma unroll
                         for (int e = 0; e < VEC; ++e)

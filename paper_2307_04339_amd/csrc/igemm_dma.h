@@ -316,10 +316,10 @@ __global__ __launch_bounds__(kWave * P, (DmaKernel<T, TM, TN, MS, P>::WAVES_PER_
                     }
                     if (m >= a.M) continue;
                     const int64_t off = yoff + m * a.ldy + n;
-                    if (a.vec_store && n + VEC <= a.Nc) {
+                    if (n + VEC <= a.Nc) {  // whole pieces; rows at any element (a.vec_store: 16 bytes)
                         Vec16<T> o;
                         if constexpr (RES) {
-                            const Vec16<T> rv = ld_vec(R + off);
+                            const Vec16<T> rv = ld_loose(R + off);
 #pragma unroll
                             for (int e = 0; e < VEC; ++e)
                                 o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e] + TypeOps<T>::to_f(rv.e[e])));
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kWave * P, (DmaKernel<T, TM, TN, MS, P>::WAVES_PER_
 #pragma unroll
                             for (int e = 0; e < VEC; ++e) o.e[e] = TypeOps<T>::from_f(act_t<T, ACT>(cr[e]));
                         }
-                        st_vec(Y + off, o);
+                        st_loose(Y + off, o);
                     } else {
 #pragma unroll
                         for (int e = 0; e < VEC; ++e)

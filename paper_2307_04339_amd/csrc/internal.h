@@ -25,7 +25,10 @@ int igemm_kernels_bf16(int cfg, int lay, const void *out[3], int *lds);
 int igemm_mi_kernels_f32(int cfg, bool uni, const void *out[3], int *lds);
 int igemm_mi_kernels_f16(int cfg, bool uni, const void *out[3], int *lds);
 int igemm_mi_kernels_bf16(int cfg, bool uni, const void *out[3], int *lds);
-// register-tile pipelined contraction: cfg CFG_PIPE_*; filters of several taps, or one tap
+// register-tile pipelined contraction: cfg CFG_PIPE_*; filters of several taps, one tap, or one tap with
+// the right operand stored [k][n]
+int pipe_kernels_nb_f16(int cfg, const void *out[3], int *lds);
+int pipe_kernels_nb_bf16(int cfg, const void *out[3], int *lds);
 int pipe_kernels_taps_f16(int cfg, const void *out[3], int *lds);
 int pipe_kernels_taps_bf16(int cfg, const void *out[3], int *lds);
 int pipe_kernels_one_f16(int cfg, const void *out[3], int *lds);

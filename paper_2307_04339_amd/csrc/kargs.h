@@ -128,12 +128,12 @@ struct RowArgs {
 enum PixKind { PIX_DW = 0, PIX_MAX = 1, PIX_AVG = 2, PIX_EW = 3, PIX_DW3 = 4 };
 constexpr int kDwStrip = 4;  // PIX_DW3: output pixels along a row per lane item
 enum RowKind { ROW_SOFTMAX = 0, ROW_LAYERNORM = 1 };
-enum IgemmLayout { LAY_VEC = 0, LAY_SCALAR = 1, LAY_VEC_NB = 2, LAY_SCALAR_NB = 3, LAY_VEC_UNI = 4, LAY_HALO = 5, LAY_RW = 6, LAY_PATCH = 7, LAY_PIPE = 8 };
+enum IgemmLayout { LAY_VEC = 0, LAY_SCALAR = 1, LAY_VEC_NB = 2, LAY_SCALAR_NB = 3, LAY_VEC_UNI = 4, LAY_HALO = 5, LAY_RW = 6, LAY_PATCH = 7, LAY_PIPE = 8, LAY_RAG_NB = 9, LAY_PIPE_NB = 10 };
 enum IgemmCfg { CFG_32 = 1, CFG_64 = 2, CFG_128 = 3, CFG_128x64 = 4, CFG_256x128 = 6, CFG_HALO = 7, CFG_RW = 8,
                 // library choice only (no descriptor code): 3x3 stride-1 patch kernel, 256 pixels x 128 / 64 channels
                 CFG_PATCH_128 = 101, CFG_PATCH_64 = 102, CFG_PATCH_64W = 103,
                 // and the register-tile pipelined contraction
-                CFG_PIPE_64 = 111, CFG_PIPE_128x64 = 112, CFG_PIPE_128 = 113, CFG_PIPE_256x128 = 114, CFG_PIPE_256x192 = 115 };
+                CFG_PIPE_64 = 111, CFG_PIPE_128x64 = 112, CFG_PIPE_128 = 113, CFG_PIPE_256x128 = 114, CFG_PIPE_256x192 = 115, CFG_PIPE_256x64 = 116 };
 // patch kernel: padded-space pixels an LDS buffer holds (the W variant: wider images)
 constexpr int kPatchPixels = 512, kPatchPixelsW = 768;
 

@@ -10,6 +10,7 @@ int igemm_kernels_bf16(int cfg, int lay, const void *out[3], int *lds) {
     case LAY_HALO: return halo_table<bf16_t>(out, lds);
     case LAY_SCALAR: return igemm_table_cfg<bf16_t, LAY_SCALAR>(cfg, out, lds);
     case LAY_VEC_NB: return igemm_table_cfg<bf16_t, LAY_VEC_NB>(cfg, out, lds);
+    case LAY_RAG_NB: return igemm_table_cfg<bf16_t, LAY_RAG_NB>(cfg, out, lds);
     case LAY_SCALAR_NB: return igemm_table_cfg<bf16_t, LAY_SCALAR_NB>(cfg, out, lds);
     default: return -1;
     }

@@ -46,21 +46,22 @@ int pix_kernels(int dtype, int kind, bool vec, const void *out[3]) {
     }
 }
 
-template <class T, int V, int KIND>
+template <class T, int KIND, bool RAG>
 static void row_table(const void *out[3]) {
-    out[0] = reinterpret_cast<const void *>(&row_kernel<T, V, KIND, 1>);
-    out[1] = reinterpret_cast<const void *>(&row_kernel<T, V, KIND, 2>);
-    out[2] = reinterpret_cast<const void *>(&row_kernel<T, V, KIND, 4>);
+    constexpr int V = 16 / sizeof(T);
+    out[0] = reinterpret_cast<const void *>(&row_kernel<T, V, KIND, 1, RAG>);
+    out[1] = reinterpret_cast<const void *>(&row_kernel<T, V, KIND, 2, RAG>);
+    out[2] = reinterpret_cast<const void *>(&row_kernel<T, V, KIND, 4, RAG>);
 }
 
+// vec: rows of whole 16-byte vectors at 16-byte addresses; otherwise any length and alignment
 template <class T>
 static int row_table_k(int kind, bool vec, const void *out[3]) {
-    constexpr int V = 16 / sizeof(T);
     switch (kind * 2 + (vec ? 1 : 0)) {
-    case 0: row_table<T, 1, ROW_SOFTMAX>(out); return 0;
-    case 1: row_table<T, V, ROW_SOFTMAX>(out); return 0;
-    case 2: row_table<T, 1, ROW_LAYERNORM>(out); return 0;
-    case 3: row_table<T, V, ROW_LAYERNORM>(out); return 0;
+    case 0: row_table<T, ROW_SOFTMAX, true>(out); return 0;
+    case 1: row_table<T, ROW_SOFTMAX, false>(out); return 0;
+    case 2: row_table<T, ROW_LAYERNORM, true>(out); return 0;
+    case 3: row_table<T, ROW_LAYERNORM, false>(out); return 0;
     default: return -1;
     }
 }

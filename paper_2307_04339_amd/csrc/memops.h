@@ -301,221 +301,263 @@ __global__ __launch_bounds__(kWave * P) void pix_kernel(PixArgs a, Shard sh) {
 }
 
 // ------------------------------------------------------------------- rows
+// What bounded the row kernels was issue, not memory: 49152 rows of 512 bf16 softmax values took
+// 27.8 us for 100 MB, of which a full expf and an IEEE division per value were most, and twelve LDS
+// permutes per row the rest.  Reductions now combine lanes with DPP moves and lane swaps in a fixed
+// order; 16-bit results take one reciprocal per row and the hardware exponential: 17 us, 5.9 TB/s.
+// Rows of any length and alignment are read in 16-byte pieces too (2 x 8 x 333 rows of 333: 7.6 ->
+// 6.5 us), the last piece of a row by element.
+
+// Sum / maximum over the wave, the same on every lane: lanes 1, 2, 4 and 8 apart by DPP (quad_perm,
+// row_half_mirror, row_mirror), 16 and 32 apart by lane swaps.
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <class F>
+__device__ __forceinline__ float wave_reduce(float v, F &&f) {
+    v = f(v, dpp_move<0xB1>(v));   // quad_perm [1, 0, 3, 2]
+    v = f(v, dpp_move<0x4E>(v));   // quad_perm [2, 3, 0, 1]
+    v = f(v, dpp_move<0x141>(v));  // row_half_mirror: the other quad of eight lanes
+    v = f(v, dpp_move<0x140>(v));  // row_mirror: the other half of sixteen
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    const auto s16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    v = f(__builtin_bit_cast(float, (uint32_t)s16[0]), __builtin_bit_cast(float, (uint32_t)s16[1]));
+    const uint32_t w = __builtin_bit_cast(uint32_t, v);
+    const auto s32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return f(__builtin_bit_cast(float, (uint32_t)s32[0]), __builtin_bit_cast(float, (uint32_t)s32[1]));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
+    return wave_reduce(v, [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-    return v;
+    return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
-// Row loads: lane handles elements j = lane*V + i*64*V (+e), in increasing i.
-template <class T, int V>
-__device__ __forceinline__ void ld_row_vec(const T *p, float *out) {
-    if constexpr (V * sizeof(T) == 16) {
-        Vec16<T> vv = ld_vec(p);
+// V consecutive values of a row, `rem` of which exist (the others read `fill`); RAG: rows of any
+// length and alignment.
+template <class T, int V, bool RAG>
+__device__ __forceinline__ void ld_row_vec(const T *p, int64_t rem, float fill, float *out) {
+    if (!RAG || rem >= V) {
+        Vec16<T> vv;
+        if constexpr (RAG) vv.u = reinterpret_cast<const Loose16 *>(p)->u;
+        else vv = ld_vec(p);
 #pragma unroll
         for (int e = 0; e < V; ++e) out[e] = TypeOps<T>::to_f(vv.e[e]);
     } else {
 #pragma unroll
-        for (int e = 0; e < V; ++e) out[e] = ld_f(p + e);
+        for (int e = 0; e < V; ++e) {  // (unconditional loads: a branch per value would wait for each in turn)
+            const float f = ld_f(p + (e < rem ? e : 0));
+            out[e] = e < rem ? f : fill;
+        }
     }
 }
-template <class T, int V>
-__device__ __forceinline__ void st_row_vec(T *p, const float *v) {
-    if constexpr (V * sizeof(T) == 16) {
+template <class T, int V, bool RAG>
+__device__ __forceinline__ void st_row_vec(T *p, int64_t rem, const float *v) {
+    if (!RAG || rem >= V) {
         Vec16<T> o;
 #pragma unroll
         for (int e = 0; e < V; ++e) o.e[e] = TypeOps<T>::from_f(v[e]);
-        st_vec(p, o);
+        if constexpr (RAG) reinterpret_cast<Loose16 *>(p)->u = o.u;
+        else st_vec(p, o);
     } else {
 #pragma unroll
-        for (int e = 0; e < V; ++e) st_f(p + e, v[e]);
+        for (int e = 0; e < V; ++e)
+            if (e < rem) st_f(p + e, v[e]);
+    }
+}
+// V floats of a per-column vector, `rem` of which exist
+template <int V, bool RAG>
+__device__ __forceinline__ void ld_cols(const float *p, int64_t rem, float *out) {
+    if (!RAG || rem >= V) {
+#pragma unroll
+        for (int q = 0; q < V / 4; ++q) {
+            const f32x4 f = reinterpret_cast<const Loose16f *>(p + 4 * q)->f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[4 * q + e] = f[e];
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < V; ++e) out[e] = p[e < rem ? e : 0];
     }
 }
 
-// Rows of up to kRowRegs vectors per lane (2048 16-bit or 1024 fp32 values) are read from
-// memory once and kept in registers for every pass; longer rows are read again per pass.
-// Either way each lane visits its elements j = lane V + i 64 V (+ e) in increasing i, so the
-// per-element operations, and the results, are the same.
+// exp(x) of a softmax term, x <= 0: 16-bit results take the hardware's exp2 of x log2 e (about 1e-6
+// relative where the term is not negligible, against a rounding of 5e-4).
+template <class T>
+__device__ __forceinline__ float soft_exp(float x) {
+    if constexpr (sizeof(T) == 2) return __builtin_amdgcn_exp2f(x * 1.44269504088896340736f);
+    else return expf(x);
+}
+
+// Lane's values of a row: j = lane V + i 64 V (+ e), in increasing i.  Rows of up to kRowRegs vectors
+// per lane (2048 16-bit or 1024 fp32 values) are read from memory once and kept in registers for
+// every pass; longer rows are read again per pass.  The per-element operations are the same.
 constexpr int kRowRegs = 4;
 
-template <class T, int V>
-__device__ void softmax_row_regs(const RowArgs &a, int64_t row, int lane) {
-    const T *xr = static_cast<const T *>(a.x) + row * a.ldx;
-    T *yr = static_cast<T *>(a.y) + row * a.ldy;
-    float v[kRowRegs][V];
-#pragma unroll
-    for (int i = 0; i < kRowRegs; ++i) {
-        const int64_t j = (int64_t)lane * V + (int64_t)i * kWave * V;
-        if (j < a.n) ld_row_vec<T, V>(xr + j, v[i]);
-    }
-    float m = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < kRowRegs; ++i) {
-        const int64_t j = (int64_t)lane * V + (int64_t)i * kWave * V;
-        if (j < a.n) {
-#pragma unroll
-            for (int e = 0; e < V; ++e) m = fmaxf(m, a.scale * v[i][e]);
-        }
-    }
-    m = wave_max(m);
-    float s = 0.0f;
-#pragma unroll
-    for (int i = 0; i < kRowRegs; ++i) {
-        const int64_t j = (int64_t)lane * V + (int64_t)i * kWave * V;
-        if (j < a.n) {
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                v[i][e] = expf(a.scale * v[i][e] - m);
-                s += v[i][e];
-            }
-        }
-    }
-    s = wave_sum(s);
-#pragma unroll
-    for (int i = 0; i < kRowRegs; ++i) {
-        const int64_t j = (int64_t)lane * V + (int64_t)i * kWave * V;
-        if (j < a.n) {
-#pragma unroll
-            for (int e = 0; e < V; ++e) v[i][e] = v[i][e] / s;
-            st_row_vec<T, V>(yr + j, v[i]);
-        }
-    }
-}
-
-template <class T, int V>
+template <class T, int V, bool RAG>
 __device__ void softmax_row(const RowArgs &a, int64_t row, int lane) {
-    if (a.n <= (int64_t)kRowRegs * kWave * V) {
-        softmax_row_regs<T, V>(a, row, lane);
-        return;
-    }
     const T *xr = static_cast<const T *>(a.x) + row * a.ldx;
     T *yr = static_cast<T *>(a.y) + row * a.ldy;
-    float m = -INFINITY;
-    for (int64_t j = (int64_t)lane * V; j < a.n; j += kWave * V) {
-        float v[V];
-        ld_row_vec<T, V>(xr + j, v);
+    const int64_t j0 = (int64_t)lane * V;
+    constexpr int64_t step = (int64_t)kWave * V;
+    // scaled values, -inf past the row's end
+    auto load = [&](int64_t j, float *v) {
+        ld_row_vec<T, V, RAG>(xr + j, a.n - j, 0.0f, v);
 #pragma unroll
-        for (int e = 0; e < V; ++e) m = fmaxf(m, a.scale * v[e]);
+        for (int e = 0; e < V; ++e) v[e] = RAG && j + e >= a.n ? -INFINITY : a.scale * v[e];
+    };
+    auto put = [&](int64_t j, const float *v, float s, float rs) {
+        float o[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) o[e] = sizeof(T) == 2 ? v[e] * rs : v[e] / s;
+        st_row_vec<T, V, RAG>(yr + j, a.n - j, o);
+    };
+    float m = -INFINITY, s = 0.0f;
+    if (a.n <= kRowRegs * step) {
+        float v[kRowRegs][V];
+#pragma unroll
+        for (int i = 0; i < kRowRegs; ++i)
+            if (j0 + i * step < a.n) load(j0 + i * step, v[i]);
+#pragma unroll
+        for (int i = 0; i < kRowRegs; ++i)
+            if (j0 + i * step < a.n) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) m = fmaxf(m, v[i][e]);
+            }
+        m = wave_max(m);
+#pragma unroll
+        for (int i = 0; i < kRowRegs; ++i)
+            if (j0 + i * step < a.n) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    v[i][e] = soft_exp<T>(v[i][e] - m);
+                    s += v[i][e];
+                }
+            }
+        s = wave_sum(s);
+        const float rs = 1.0f / s;
+#pragma unroll
+        for (int i = 0; i < kRowRegs; ++i)
+            if (j0 + i * step < a.n) put(j0 + i * step, v[i], s, rs);
+        return;
+    }
+    float v[V];
+    for (int64_t j = j0; j < a.n; j += step) {
+        load(j, v);
+#pragma unroll
+        for (int e = 0; e < V; ++e) m = fmaxf(m, v[e]);
     }
     m = wave_max(m);
-    float s = 0.0f;
-    for (int64_t j = (int64_t)lane * V; j < a.n; j += kWave * V) {
-        float v[V];
-        ld_row_vec<T, V>(xr + j, v);
+    for (int64_t j = j0; j < a.n; j += step) {
+        load(j, v);
 #pragma unroll
-        for (int e = 0; e < V; ++e) s += expf(a.scale * v[e] - m);
+        for (int e = 0; e < V; ++e) s += soft_exp<T>(v[e] - m);
     }
     s = wave_sum(s);
-    for (int64_t j = (int64_t)lane * V; j < a.n; j += kWave * V) {
-        float v[V];
-        ld_row_vec<T, V>(xr + j, v);
+    const float rs = 1.0f / s;
+    for (int64_t j = j0; j < a.n; j += step) {
+        load(j, v);
 #pragma unroll
-        for (int e = 0; e < V; ++e) v[e] = expf(a.scale * v[e] - m) / s;
-        st_row_vec<T, V>(yr + j, v);
+        for (int e = 0; e < V; ++e) v[e] = soft_exp<T>(v[e] - m);
+        put(j, v, s, rs);
     }
 }
 
-template <class T, int V>
-__device__ void layernorm_row_regs(const RowArgs &a, int64_t row, int lane) {
-    const T *xr = static_cast<const T *>(a.x) + row * a.ldx;
-    const T *rr = static_cast<const T *>(a.res) + row * a.ldx;
-    T *yr = static_cast<T *>(a.y) + row * a.ldy;
-    float v[kRowRegs][V];
-#pragma unroll
-    for (int i = 0; i < kRowRegs; ++i) {
-        const int64_t j = (int64_t)lane * V + (int64_t)i * kWave * V;
-        if (j < a.n) {
-            ld_row_vec<T, V>(xr + j, v[i]);
-            if (a.has_res) {
-                float r[V];
-                ld_row_vec<T, V>(rr + j, r);
-#pragma unroll
-                for (int e = 0; e < V; ++e) v[i][e] += r[e];
-            }
-        }
-    }
-    float s = 0.0f;
-#pragma unroll
-    for (int i = 0; i < kRowRegs; ++i) {
-        const int64_t j = (int64_t)lane * V + (int64_t)i * kWave * V;
-        if (j < a.n) {
-#pragma unroll
-            for (int e = 0; e < V; ++e) s += v[i][e];
-        }
-    }
-    const float mean = wave_sum(s) / (float)a.n;
-    float q = 0.0f;
-#pragma unroll
-    for (int i = 0; i < kRowRegs; ++i) {
-        const int64_t j = (int64_t)lane * V + (int64_t)i * kWave * V;
-        if (j < a.n) {
-#pragma unroll
-            for (int e = 0; e < V; ++e) q += (v[i][e] - mean) * (v[i][e] - mean);
-        }
-    }
-    const float var = wave_sum(q) / (float)a.n;
-    const float rstd = 1.0f / sqrtf(var + a.eps);
-#pragma unroll
-    for (int i = 0; i < kRowRegs; ++i) {
-        const int64_t j = (int64_t)lane * V + (int64_t)i * kWave * V;
-        if (j < a.n) {
-#pragma unroll
-            for (int e = 0; e < V; ++e) v[i][e] = (v[i][e] - mean) * rstd * a.gamma[j + e] + a.beta[j + e];
-            st_row_vec<T, V>(yr + j, v[i]);
-        }
-    }
-}
-
-template <class T, int V>
+template <class T, int V, bool RAG>
 __device__ void layernorm_row(const RowArgs &a, int64_t row, int lane) {
-    if (a.n <= (int64_t)kRowRegs * kWave * V) {
-        layernorm_row_regs<T, V>(a, row, lane);
-        return;
-    }
     const T *xr = static_cast<const T *>(a.x) + row * a.ldx;
     const T *rr = static_cast<const T *>(a.res) + row * a.ldx;
     T *yr = static_cast<T *>(a.y) + row * a.ldy;
+    const int64_t j0 = (int64_t)lane * V;
+    constexpr int64_t step = (int64_t)kWave * V;
     auto load = [&](int64_t j, float *v) {
-        ld_row_vec<T, V>(xr + j, v);
+        ld_row_vec<T, V, RAG>(xr + j, a.n - j, 0.0f, v);
         if (a.has_res) {
             float r[V];
-            ld_row_vec<T, V>(rr + j, r);
+            ld_row_vec<T, V, RAG>(rr + j, a.n - j, 0.0f, r);
 #pragma unroll
             for (int e = 0; e < V; ++e) v[e] += r[e];
         }
     };
-    float s = 0.0f;
-    for (int64_t j = (int64_t)lane * V; j < a.n; j += kWave * V) {
-        float v[V];
+    // sum of squared deviations of the values that exist
+    auto square = [&](int64_t j, const float *v, float mean) {
+        float q = 0.0f;
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (!RAG || j + e < a.n) q += (v[e] - mean) * (v[e] - mean);
+        return q;
+    };
+    auto put = [&](int64_t j, float *v, const float *g, const float *b, float mean, float rstd) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) v[e] = (v[e] - mean) * rstd * g[e] + b[e];
+        st_row_vec<T, V, RAG>(yr + j, a.n - j, v);
+    };
+    float s = 0.0f, q = 0.0f;
+    if (a.n <= kRowRegs * step) {
+        // the row and the column parameters of its first kColRegs vectors per lane are requested
+        // before the first reduction (of all of them, the registers would halve the waves in flight)
+        constexpr int kColRegs = 2;
+        float v[kRowRegs][V], g[kColRegs][V], b[kColRegs][V];
+#pragma unroll
+        for (int i = 0; i < kRowRegs; ++i) {
+            const int64_t j = j0 + i * step;
+            if (j < a.n) {
+                load(j, v[i]);
+                if (i < kColRegs) {
+                    ld_cols<V, RAG>(a.gamma + j, a.n - j, g[i]);
+                    ld_cols<V, RAG>(a.beta + j, a.n - j, b[i]);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kRowRegs; ++i)
+            if (j0 + i * step < a.n) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) s += v[i][e];
+            }
+        const float mean = wave_sum(s) / (float)a.n;
+#pragma unroll
+        for (int i = 0; i < kRowRegs; ++i)
+            if (j0 + i * step < a.n) q += square(j0 + i * step, v[i], mean);
+        const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)a.n + a.eps);
+#pragma unroll
+        for (int i = 0; i < kRowRegs; ++i) {
+            const int64_t j = j0 + i * step;
+            if (j < a.n) {
+                if (i < kColRegs) {
+                    put(j, v[i], g[i], b[i], mean, rstd);
+                } else {
+                    float gl[V], bl[V];
+                    ld_cols<V, RAG>(a.gamma + j, a.n - j, gl);
+                    ld_cols<V, RAG>(a.beta + j, a.n - j, bl);
+                    put(j, v[i], gl, bl, mean, rstd);
+                }
+            }
+        }
+        return;
+    }
+    float v[V], g[V], b[V];
+    for (int64_t j = j0; j < a.n; j += step) {
         load(j, v);
 #pragma unroll
         for (int e = 0; e < V; ++e) s += v[e];
     }
     const float mean = wave_sum(s) / (float)a.n;
-    float q = 0.0f;
-    for (int64_t j = (int64_t)lane * V; j < a.n; j += kWave * V) {
-        float v[V];
+    for (int64_t j = j0; j < a.n; j += step) {
         load(j, v);
-#pragma unroll
-        for (int e = 0; e < V; ++e) q += (v[e] - mean) * (v[e] - mean);
+        q += square(j, v, mean);
     }
-    const float var = wave_sum(q) / (float)a.n;
-    const float rstd = 1.0f / sqrtf(var + a.eps);
-    for (int64_t j = (int64_t)lane * V; j < a.n; j += kWave * V) {
-        float v[V];
+    const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)a.n + a.eps);
+    for (int64_t j = j0; j < a.n; j += step) {
         load(j, v);
-#pragma unroll
-        for (int e = 0; e < V; ++e) v[e] = (v[e] - mean) * rstd * a.gamma[j + e] + a.beta[j + e];
-        st_row_vec<T, V>(yr + j, v);
+        ld_cols<V, RAG>(a.gamma + j, a.n - j, g);
+        ld_cols<V, RAG>(a.beta + j, a.n - j, b);
+        put(j, v, g, b, mean, rstd);
     }
 }
 
-template <class T, int V, int KIND, int P>
+template <class T, int V, int KIND, int P, bool RAG>
 __global__ __launch_bounds__(kWave * P) void row_kernel(RowArgs a, Shard sh) {
     const int pw = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
@@ -529,8 +571,8 @@ __global__ __launch_bounds__(kWave * P) void row_kernel(RowArgs a, Shard sh) {
             trace_wave(sh, t, lam, pw, s);
             const int64_t row = t * kLogicalWaves + lam;
             if (row >= a.rows) continue;
-            if constexpr (KIND == ROW_SOFTMAX) softmax_row<T, V>(a, row, lane);
-            else layernorm_row<T, V>(a, row, lane);
+            if constexpr (KIND == ROW_SOFTMAX) softmax_row<T, V, RAG>(a, row, lane);
+            else layernorm_row<T, V, RAG>(a, row, lane);
         }
     }
 }

@@ -92,7 +92,7 @@ static void query_occupancy(miriam_op *op) {
         op->full_grid = std::min<int64_t>(op->T, (int64_t)device_cus() * op->max_wg_per_cu[2]);
     // the patch kernel loads the next tile's first operands under the current tile's epilogue: as
     // few workgroups as keep the number of rounds
-    if (op->family == FAM_IGEMM && (op->lay == LAY_PATCH || op->lay == LAY_PIPE) && op->max_wg_per_cu[2] > 0)
+    if (op->family == FAM_IGEMM && (op->lay == LAY_PATCH || op->lay == LAY_PIPE || op->lay == LAY_PIPE_NB) && op->max_wg_per_cu[2] > 0)
         op->full_grid = cdiv(op->T, cdiv(op->T, (int64_t)device_cus() * op->max_wg_per_cu[2]));
     // the pipelined contraction with more tiles than resident workgroups, but at most twice as
     // many: half as many workgroups, two tiles each, none waiting for a second dispatch (VGG-16
@@ -163,7 +163,8 @@ static int choose_cfg(int64_t batch, int64_t M, int64_t N, int64_t k_chunks) {
 
 static int patch_tile_n(int cfg) { return cfg == CFG_PATCH_128 ? 128 : 64; }
 
-static int get_pipe_table(int dtype, bool taps, int cfg, const void *out[3], int *lds) {
+static int get_pipe_table(int dtype, bool taps, bool nmaj, int cfg, const void *out[3], int *lds) {
+    if (nmaj) return (dtype == MIRIAM_F16 ? pipe_kernels_nb_f16 : pipe_kernels_nb_bf16)(cfg, out, lds);
     switch (dtype) {
     case MIRIAM_F16: return (taps ? pipe_kernels_taps_f16 : pipe_kernels_one_f16)(cfg, out, lds);
     case MIRIAM_BF16: return (taps ? pipe_kernels_taps_bf16 : pipe_kernels_one_bf16)(cfg, out, lds);
@@ -172,7 +173,9 @@ static int get_pipe_table(int dtype, bool taps, int cfg, const void *out[3], int
 }
 
 static int pipe_tile_m(int cfg) { return cfg == CFG_PIPE_64 ? 64 : (cfg == CFG_PIPE_128x64 || cfg == CFG_PIPE_128 ? 128 : 256); }
-static int pipe_tile_n(int cfg) { return cfg == CFG_PIPE_256x192 ? 192 : (cfg == CFG_PIPE_64 || cfg == CFG_PIPE_128x64 ? 64 : 128); }
+static int pipe_tile_n(int cfg) {
+    return cfg == CFG_PIPE_256x192 ? 192 : (cfg == CFG_PIPE_64 || cfg == CFG_PIPE_128x64 || cfg == CFG_PIPE_256x64 ? 64 : 128);
+}
 
 // Register-tile pipelined contraction (gemm_pipe.h) for fp16 / bf16 with whole 16-byte output pieces
 // and 32-bit offsets per batch entry: CFG_PIPE_*, or 0 where igemm_dma_kernel stays.  The tile with
@@ -182,26 +185,28 @@ static int pipe_tile_n(int cfg) { return cfg == CFG_PIPE_256x192 ? 192 : (cfg ==
 // CU).  Measured back to back in a captured graph, bf16, igemm_dma_kernel -> this: 4096x2304x768 28.9
 // -> 23.3 us (256x192), 4096x768x3072 31.7 -> 26.3 (128x128), 2048x2304x768 20.7 -> 16.2 (256x128),
 // 2048x768x3072 22.0 -> 19.0 (128x64), 8x56x56x128->256 3x3/2 12.7 -> 10.9 (128x64), 16x7x7x160->960
-// 1x1 6.7 -> 4.8 (64x64).  Few small tiles with long K stay there, where it splits K or takes 32x32
+// 1x1 6.7 -> 4.8 (64x64).  [k][n] right operands (attention's P V, bf16, from the register-staged
+// kernel): 96 x 512x64x512 19.0 -> 14.6 us (256x64), 48 x 256x64x256 7.0 -> 5.1 (64x64).  Few small tiles with long K stay there, where it splits K or takes 32x32
 // tiles: 104 tiles of 1x28x28x256->512 12.0 against 12.8, 200 tiles of 8x14x14x512->512 20.4 (two
 // slices) against 22.9; up to 12 chunks the line is a quarter of the CUs, 72 tiles of 128x2304x768
 // 6.7 -> 6.6, 49 of 16x14x14x384->64 4.8 against 5.3.
-static int choose_pipe(const miriam_op_desc &d, const IgemmArgs &a, int64_t batch) {
+static int choose_pipe(const miriam_op_desc &d, const IgemmArgs &a, int64_t batch, bool nmaj) {
     const int64_t es = esize(d.dtype), lim = (int64_t)1 << 31, kt = 128 / es;
     const bool taps = a.KH * a.KW > 1;
     if (d.dtype == MIRIAM_F32 || !a.vec_store || a.Nc % 8 != 0 || (taps && a.C % kt != 0)) return 0;
-    if ((d.kind == MIRIAM_OP_CONV2D ? d.n * a.img_x : (a.M - 1) * a.ldx + a.K) * es >= lim || ((a.Nc - 1) * a.ldw + a.K) * es >= lim ||
-        ((a.M - 1) * a.ldy + a.Nc) * es >= lim)
+    if ((d.kind == MIRIAM_OP_CONV2D ? d.n * a.img_x : (a.M - 1) * a.ldx + a.K) * es >= lim ||
+        (nmaj ? (a.K - 1) * a.ldw + a.Nc : (a.Nc - 1) * a.ldw + a.K) * es >= lim || ((a.M - 1) * a.ldy + a.Nc) * es >= lim)
         return 0;
     const int64_t cus = device_cus(), nch = cdiv(a.K, kt), t64 = batch * cdiv(a.M, 64) * cdiv(a.Nc, 64);
     if (t64 * (nch <= 12 ? 4 : 2) < cus) return 0;
     struct Cost { int cfg; int64_t chunk, rest; };
-    static const Cost costs[5] = {{CFG_PIPE_64, 220, 1800}, {CFG_PIPE_128x64, 276, 2500}, {CFG_PIPE_128, 420, 3500},
-                                  {CFG_PIPE_256x128, 830, 4500}, {CFG_PIPE_256x192, 1350, 6000}};
+    static const Cost costs[6] = {{CFG_PIPE_64, 220, 1800}, {CFG_PIPE_128x64, 276, 2500}, {CFG_PIPE_128, 420, 3500},
+                                  {CFG_PIPE_256x128, 830, 4500}, {CFG_PIPE_256x192, 1350, 6000}, {CFG_PIPE_256x64, 460, 3500}};
     int best = 0;
     int64_t least = INT64_MAX;
     for (const Cost &c : costs) {
         if (taps && c.cfg == CFG_PIPE_256x192) continue;
+        if (nmaj ? pipe_tile_n(c.cfg) != 64 : c.cfg == CFG_PIPE_256x64) continue;
         const int64_t tiles = batch * cdiv(a.M, pipe_tile_m(c.cfg)) * cdiv(a.Nc, pipe_tile_n(c.cfg));
         const int64_t ns = cdiv(tiles, cus) * (nch * c.chunk + c.rest);
         if (ns < least) {
@@ -453,8 +458,8 @@ static int create_igemm(miriam_op *op) {
     if (cfg == 0 && rw_fits) cfg = CFG_RW;
     if (cfg == 0 && halo_fits) cfg = CFG_HALO;
     if (cfg == 0) cfg = (skinny_ok && !memidx) ? TILE_SKINNY : choose_cfg(batch, a.M, a.Nc, cdiv(a.K * es, 128));
-    if (d.tile == 0 && !memidx && !nmaj && a_vec && b_vec && d.ksplit <= 1 && cfg >= CFG_32 && cfg <= CFG_128x64) {
-        pipe = choose_pipe(d, a, batch);
+    if (d.tile == 0 && !memidx && a_vec && b_vec && d.ksplit <= 1 && cfg >= CFG_32 && cfg <= CFG_128x64) {
+        pipe = choose_pipe(d, a, batch, nmaj);
         if (pipe) cfg = pipe;
     }
     if (memidx && (cfg == CFG_RW || cfg == CFG_HALO || cfg == TILE_SKINNY))
@@ -470,13 +475,13 @@ static int create_igemm(miriam_op *op) {
         a.ksplit = 1;
         a.cps = 1;
         a.x_bytes = (uint32_t)((d.kind == MIRIAM_OP_CONV2D ? d.n * a.img_x : (a.M - 1) * a.ldx + a.K) * es);
-        a.w_bytes = (uint32_t)(((a.Nc - 1) * a.ldw + a.K) * es);
+        a.w_bytes = (uint32_t)((nmaj ? (a.K - 1) * a.ldw + a.Nc : (a.Nc - 1) * a.ldw + a.K) * es);
         a.y_bytes = (uint32_t)(((a.M - 1) * a.ldy + a.Nc) * es);
         op->cfg = cfg;
         op->tile_m = pipe_tile_m(pipe);
         op->tile_n = pipe_tile_n(pipe);
-        op->lay = LAY_PIPE;
-        if (get_pipe_table(d.dtype, a.KH * a.KW > 1, cfg, op->kern, &op->lds_bytes) != 0)
+        op->lay = nmaj ? LAY_PIPE_NB : LAY_PIPE;
+        if (get_pipe_table(d.dtype, a.KH * a.KW > 1, nmaj, cfg, op->kern, &op->lds_bytes) != 0)
             return einval("no register-tile kernel for this tile");
     } else if (patch && cfg == patch) {
         a.sx0 = patch_group;
@@ -624,7 +629,7 @@ static int create_igemm(miriam_op *op) {
         op->cfg = cfg;
         op->tile_m = tile_m_of(cfg);
         op->tile_n = tile_n_of(cfg);
-        if (nmaj) op->lay = (a_vec && b_vec) ? LAY_VEC_NB : LAY_SCALAR_NB;
+        if (nmaj) op->lay = !b_vec ? LAY_SCALAR_NB : (a_vec ? LAY_VEC_NB : LAY_RAG_NB);
         else op->lay = (a_vec && b_vec) ? LAY_VEC : LAY_SCALAR;
         // every 128-byte K chunk inside one filter tap: per-lane pointers advance per chunk
         // the chunk-uniform decode reads its operands as buffers with 32-bit offsets: spans in
@@ -960,9 +965,9 @@ int miriam_op_query(const miriam_op *op, miriam_op_info *out) {
         out->path = op->lay == LAY_RW        ? MIRIAM_PATH_RESIDENT
                     : op->lay == LAY_HALO    ? MIRIAM_PATH_HALO
                     : op->lay == LAY_VEC_UNI || op->lay == LAY_PATCH ||
-                            (op->lay == LAY_PIPE && op->ig.C % (128 / esize(op->d.dtype)) == 0)
+                            ((op->lay == LAY_PIPE || op->lay == LAY_PIPE_NB) && op->ig.C % (128 / esize(op->d.dtype)) == 0)
                         ? MIRIAM_PATH_DMA_UNIFORM
-                    : op->lay == LAY_VEC || op->lay == LAY_PIPE ? MIRIAM_PATH_DMA
+                    : op->lay == LAY_VEC || op->lay == LAY_PIPE || op->lay == LAY_PIPE_NB ? MIRIAM_PATH_DMA
                                              : MIRIAM_PATH_STAGED;
     else out->path = MIRIAM_PATH_OTHER;
     out->ksplit = (op->family == FAM_IGEMM || op->family == FAM_SKINNY) ? op->ig.ksplit : 1;

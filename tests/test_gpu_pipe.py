@@ -121,3 +121,55 @@ def test_pipe_batched_scores_match_oracle(ops, orc, B, H, S, tile):
     ref = np.einsum("bihd,bjhd->bhij", q[:, :, 0], q[:, :, 1]).reshape(B * H, S, S)
     assert rel_err(to_f64(y), ref) <= TOL["bf16"]
     _elastic(op, y, orc)
+
+
+# attention's probabilities times values ([k][n] right operand); odd lengths go through the
+# register-staged kernel, which reads the probabilities' rows in unaligned 16-byte pieces
+@pytest.mark.parametrize("B,H,S,tile", [(4, 8, 136, (64, 64)), (13, 12, 128, (128, 64)), (12, 12, 256, (256, 64)),
+                                        (3, 4, 131, None), (2, 3, 9, None)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_batched_context_matches_oracle_and_is_elastic(ops, orc, dtype, B, H, S, tile):
+    from paper_2307_04339_amd import _lib as L
+    D = 64
+    p, p64 = rand((B * H, S, S), dtype, seed=6, lo=0.0, hi=1.0)
+    qkv, q64 = rand((B * S, 3 * H * D), dtype, seed=7)
+    y = empty((B * S, H * D), dtype)
+    op = ops.bgemm(p, qkv[:, 2 * H * D:], y, m=S, n=D, k=S, batch=B * H, batch_div=H, ldx=S, ldw=3 * H * D, ldy=H * D,
+                   sx=(H * S * S, S * S), sw=(S * 3 * H * D, D), sy=(S * H * D, D), b_nmajor=True)
+    if tile:
+        assert _is_pipe(op, tile), (op.info.path, op.info.tile_m, op.info.tile_n, op.info.lds_bytes)
+    else:
+        assert op.info.path == L.PATH_STAGED
+    op.run()
+    torch.cuda.synchronize()
+    v = q64.reshape(B, S, 3, H, D)[:, :, 2]
+    ref = np.einsum("bhij,bjhd->bihd", p64.reshape(B, H, S, S), v).reshape(B * S, H * D)
+    err = rel_err(to_f64(y), ref)
+    print(f"context {dtype} {B}x{H}x{S}: T={op.T} rel={err:.3e}")
+    assert err <= TOL[dtype], err
+    _elastic(op, y, orc)
+
+
+@pytest.mark.parametrize("n", [1, 3, 8, 77, 333, 512, 520, 2047, 2056])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_rows_of_any_length_match_oracle(ops, orc, dtype, n):
+    tol = {"f32": 1e-5, **TOL}[dtype]
+    rows = 13
+    x, x64 = rand((rows, n + 3), dtype, seed=8, lo=-3, hi=3)
+    x[5, :] = torch.finfo(x.dtype).min  # a fully masked row: uniform probabilities
+    x64 = to_f64(x)
+    y = empty((rows, n + 5), dtype)
+    ops.softmax(x, y, rows, n, scale=1.0, ldx=n + 3, ldy=n + 5).run()
+    torch.cuda.synchronize()
+    got = to_f64(y)
+    assert np.isnan(got[:, n:]).all()  # nothing past the rows' ends
+    assert rel_err(got[:, :n], orc.softmax_rows(np.ascontiguousarray(x64[:, :n]), 1.0)) <= tol
+    z, z64 = rand((rows, n), dtype, seed=9, lo=-2, hi=2)
+    r, r64 = rand((rows, n), dtype, seed=10)
+    rng = np.random.default_rng(11)
+    g, b = (rng.uniform(0.5, 1.5, n).astype(np.float32).astype(np.float64) for _ in range(2))
+    o = empty((rows, n), dtype)
+    ops.layernorm(z, f32_dev(g), f32_dev(b), o, rows, n, residual=r, eps=1e-2).run()
+    torch.cuda.synchronize()
+    # values near +-3 on parameters near 1.5: a few fp32 ulps more than the output's rounding
+    assert rel_err(to_f64(o), orc.layernorm_rows(z64 + r64, g, b, 1e-2)) <= tol + 1e-5
