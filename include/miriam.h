@@ -227,6 +227,10 @@ int miriam_op_query(const miriam_op *op, miriam_op_info *out);
 int miriam_elastic_launch(const miriam_op *op, int64_t shard_begin, int64_t shard_len,
                           int grid, int block, void *stream);
 
+/* The op's unsharded launch: the whole tile space with miriam_op_info.full_grid workgroups of 256
+ * threads, as miriam_elastic_launch(op, 0, num_tiles, full_grid, 256, stream) queues it. */
+int miriam_op_run(const miriam_op *op, void *stream);
+
 /*
  * Same launch, additionally recording for every tile t of the shard, in caller-owned
  * device arrays of T int32 entries: owner_wg[t] = physical workgroup, owner_iter[t] =

@@ -981,6 +981,11 @@ int miriam_elastic_launch(const miriam_op *op, int64_t shard_begin, int64_t shar
                      nullptr, nullptr, nullptr, nullptr);
 }
 
+int miriam_op_run(const miriam_op *op, void *stream) {
+    if (!op) return einval("null op");
+    return op_launch(op, 0, op->T, op_full_grid(op), 256, static_cast<hipStream_t>(stream));
+}
+
 int miriam_elastic_launch_traced(const miriam_op *op, int64_t shard_begin, int64_t shard_len, int grid,
                                  int block, void *stream, int32_t *owner_wg, int32_t *owner_iter,
                                  int32_t *count, int32_t *wave_phys, int32_t *wave_slot) {

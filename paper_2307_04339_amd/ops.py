@@ -19,10 +19,18 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# The current stream's handle without building a torch Stream object, which costs 2.7 us of a 6.4 us
+# launch (0.2 us this way); the object where this torch build has no raw accessor.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_handle(stream):
     if stream is None:
+        if _raw_stream is not None and _device is not None:
+            return _raw_stream(_device())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 class ElasticOp:
@@ -89,7 +97,9 @@ class ElasticOp:
     def run(self, stream=None) -> None:
         """Unsharded launch: the whole tile space at the op's full grid (one workgroup per
         tile, or the resident capacity for kernels that keep operands across tiles), block 256."""
-        self.launch(0, self.T, int(self.info.full_grid), 256, stream)
+        rc = L.load().miriam_op_run(self.handle, _stream_handle(stream))
+        if rc < 0:
+            L.check(rc, "miriam_op_run")
 
     def run_plan(self, shards, grids, blocks, stream=None) -> None:
         for (b, l), g, bl in zip(shards, grids, blocks):
