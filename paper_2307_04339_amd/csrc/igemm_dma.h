@@ -449,6 +449,45 @@ __global__ __launch_bounds__(kWave * P, (DmaKernel<T, TM, TN, MS, P>::WAVES_PER_
                 const char *sta = smem + (SR ? (ch % K_::SA) * K_::A_STAGE : (ch % S) * K_::STAGE);
                 const char *stb = smem + (SR ? K_::SA * K_::A_STAGE + (ch % K_::SB) * K_::B_STAGE
                                              : (ch % S) * K_::STAGE + TM * 128);
+                if constexpr (sizeof(T) == 4) {
+                    // fp32: a lane reads whole 16-byte pieces, four K values, and MFMA e of a piece
+                    // takes value e of every lane's (K order within a chunk: piece group, then e, then the
+                    // lanes' K halves), a quarter of the LDS reads of one value per MFMA (3x3 of
+                    // 56x56x64 to 64 10.2 to 9.1 us, 8x56x56x64 to 64 29.7 to 27.3, 14x14x256 to 256 11.9 to 10.8)
+                    constexpr int LG = kWave / MS, NG = 8 / LG;  // lanes along K, piece groups per chunk
+                    f32x4 aop[NG][SL][BM], bop[NG][SL][BN];
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) {
+                        const int piece = g * LG + lane / MS;
+#pragma unroll
+                        for (int s = 0; s < SL; ++s) {
+                            const int lam = (rd * SL + s) * P + pw;
+                            const int wm = lam >> 1, wn = lam & 1;
+#pragma unroll
+                            for (int jn = 0; jn < BN; ++jn) {
+                                const int row = wn * (TN / 2) + jn * MS + lane % MS;
+                                bop[g][s][jn] = *reinterpret_cast<const f32x4 *>(stb + row * 128 + ((piece ^ ((row >> 1) & 7)) * 16));
+                            }
+#pragma unroll
+                            for (int i = 0; i < BM; ++i) {
+                                const int row = wm * (TM / 2) + i * MS + lane % MS;
+                                aop[g][s][i] = *reinterpret_cast<const f32x4 *>(sta + row * 128 + ((piece ^ ((row >> 1) & 7)) * 16));
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int g = 0; g < NG; ++g)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+#pragma unroll
+                            for (int s = 0; s < SL; ++s)
+#pragma unroll
+                                for (int i = 0; i < BM; ++i)
+#pragma unroll
+                                    for (int jn = 0; jn < BN; ++jn)
+                                        acc[s][i][jn] = MF::run(aop[g][s][i][e], bop[g][s][jn][e], acc[s][i][jn]);
+                    return;
+                } else {
                 constexpr int NK = KT / KSTEP;
                 // read every operand of the chunk first, so LDS latency overlaps the MFMAs
                 op_t aop[NK][SL][BM], bop[NK][SL][BN];
@@ -491,6 +530,7 @@ __global__ __launch_bounds__(kWave * P, (DmaKernel<T, TM, TN, MS, P>::WAVES_PER_
                 for (int kk = 0; kk < NK; ++kk) {
                     __builtin_amdgcn_sched_group_barrier(0x008, MM, 0);
                     if (kk + 2 < NK) __builtin_amdgcn_sched_group_barrier(0x100, RD, 0);
+                }
                 }
             };
 
