@@ -1,6 +1,6 @@
 // Direct convolution with the weights resident in registers, for narrow layers (fp16 /
-// bf16, C <= 64 input channels): 3x3 stride 1 (at most 64 output channels), 3x3 stride 2
-// (8-channel images), and 1x1 stride 1 (any number of output channels).
+// bf16, C <= 64 input channels): here 3x3 stride 1 (at most 64 output channels); 3x3 stride 2
+// (8-channel images) and 1x1 stride 1 (any number of output channels) in conv_rw_regs.h.
 //
 // The tile is 4 x 32 output pixels of one image times 64 output channels (for 3x3 stride 1
 // the tile of the LDS-patch kernel, so the tile space, the shard plans and the tile map
@@ -423,34 +423,16 @@ inline void rw_table(const void *out[3], int *lds) {
     *lds = RwKernel<T, C, 4, KS, ST>::LDS_BYTES;
 }
 
-// Kernel table of the resident-weight kernel for a (kernel size, stride, C) it serves:
-// 3x3 stride 1 with C in {8, 16, 32, 64}, 3x3 stride 2 with C = 8, 1x1 with C in
-// {16, 24, 32, 64}; -1 otherwise.
+// Kernel table for 3x3 stride 1 with C in {8, 16, 32, 64}; -1 otherwise.
 template <class T>
-inline int rw_table_c(int64_t ks, int64_t st, int64_t c, const void *out[3], int *lds) {
-    if (ks == 3 && st == 1) {
-        switch (c) {
-        case 8: rw_table<T, 8, 3, 1>(out, lds); return 0;
-        case 16: rw_table<T, 16, 3, 1>(out, lds); return 0;
-        case 32: rw_table<T, 32, 3, 1>(out, lds); return 0;
-        case 64: rw_table<T, 64, 3, 1>(out, lds); return 0;
-        default: return -1;
-        }
+inline int rw_table_c(int64_t c, const void *out[3], int *lds) {
+    switch (c) {
+    case 8: rw_table<T, 8, 3, 1>(out, lds); return 0;
+    case 16: rw_table<T, 16, 3, 1>(out, lds); return 0;
+    case 32: rw_table<T, 32, 3, 1>(out, lds); return 0;
+    case 64: rw_table<T, 64, 3, 1>(out, lds); return 0;
+    default: return -1;
     }
-    if (ks == 3 && st == 2 && c == 8) {
-        rw_table<T, 8, 3, 2>(out, lds);
-        return 0;
-    }
-    if (ks == 1 && st == 1) {
-        switch (c) {
-        case 16: rw_table<T, 16, 1, 1>(out, lds); return 0;
-        case 24: rw_table<T, 24, 1, 1>(out, lds); return 0;
-        case 32: rw_table<T, 32, 1, 1>(out, lds); return 0;
-        case 64: rw_table<T, 64, 1, 1>(out, lds); return 0;
-        default: return -1;
-        }
-    }
-    return -1;
 }
 
 }  // namespace miriam

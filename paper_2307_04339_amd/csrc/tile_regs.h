@@ -99,7 +99,9 @@ __device__ __forceinline__ void exchange16(u32x4 &a, u32x4 &b) {
 // row into one store: 64 contiguous bytes per row (32 without it: 96 x 512 x 512 x 64 products, all
 // stores, 23.8 us at 256x128 against 22.9 for LDS-staged whole rows).  Every wave issues the same
 // stores; pieces outside take an offset past the buffer.
-template <class T, class Acc, int BP, int BC, class Rows>
+// KEEP: a column block's scales and shifts stay in registers for all its row blocks; without it they are
+// read with each quarter (a kernel that has no 32 registers to spare).
+template <class T, bool KEEP = true, class Acc, int BP, int BC, class Rows>
 __device__ __forceinline__ void finish_tile(const Epilogue &e, const char *aff0, int TN, int nl0, uint32_t n0, uint32_t Nc,
                                             __amdgpu_buffer_rsrc_t ry, __amdgpu_buffer_rsrc_t rr, Acc (&acc)[BP][BC], Rows &&row_of) {
     const int lane = threadIdx.x % kWave, hx = lane >> 5;
@@ -111,10 +113,13 @@ __device__ __forceinline__ void finish_tile(const Epilogue &e, const char *aff0,
             const int nl = nl0 + c * 32;
             const float *aff = reinterpret_cast<const float *>(aff0) + nl + 4 * hx;
             f32x4 sc[4], shf[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            auto affine = [&](int g) {
                 sc[g] = *reinterpret_cast<const f32x4 *>(aff + 8 * g);
                 shf[g] = *reinterpret_cast<const f32x4 *>(aff + TN + 8 * g);
+            };
+            if constexpr (KEEP) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) affine(g);
             }
 #pragma unroll
             for (int b = 0; b < BP; ++b) {
@@ -123,6 +128,7 @@ __device__ __forceinline__ void finish_tile(const Epilogue &e, const char *aff0,
                     const bool in = row_of(b, lane & 31, row);
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
+                        if constexpr (!KEEP) affine(g);
                         const uint32_t n = n0 + (uint32_t)(nl + 8 * g + 4 * hx);
                         const uint32_t off = in & (n < Nc) ? (row + n) * 4u : kOutOfRange;
                         f32x4 r = {0.0f, 0.0f, 0.0f, 0.0f}, o;
@@ -164,7 +170,8 @@ __device__ __forceinline__ void finish_tile(const Epilogue &e, const char *aff0,
                             }
                         }
 #pragma unroll
-                        for (int w = 0; w < 2; ++w)
+                        for (int w = 0; w < 2; ++w) {
+                            if constexpr (!KEEP) affine(2 * h + w);
 #pragma unroll
                             for (int k = 0; k < 2; ++k) {
                                 f32x2 v2;
@@ -179,6 +186,7 @@ __device__ __forceinline__ void finish_tile(const Epilogue &e, const char *aff0,
                                 typedef T t2 __attribute__((ext_vector_type(2)));
                                 q[w][k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v2, t2));
                             }
+                        }
 #pragma unroll
                         for (int k = 0; k < 2; ++k) {
                             const auto sw = __builtin_amdgcn_permlane32_swap(q[0][k], q[1][k], false, false);
