@@ -275,7 +275,13 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
             static_for<LA>([&](auto k) {
                 static_for<NOP>([&](auto i) { fetch1(decltype(i)::value, decltype(k)::value, 0u, decltype(k)::value); });
             });
-            if (rd == 0) make_affine(a.epi, smem_ + K_::RAW0, smem_ + K_::AFF0, TN, tid, K_::NT);
+            if (rd == 0) {
+                make_affine(a.epi, smem_ + K_::RAW0, smem_ + K_::AFF0, TN, tid, K_::NT);
+                // With LA = 3 the meetings of the chunk loop leave LDS operations outstanding; for a
+                // single chunk the first of them is all that stands between this write and the other
+                // waves' epilogue.  LA = 1: every meeting waits for them.
+                if constexpr (LA > 1) wait_lds();
+            }
             __builtin_amdgcn_sched_barrier(0);
             int slot = 0;                                        // stage of the current chunk
             uint32_t refill = stage_of(AHEAD - 1);               // stage the loads in progress go to

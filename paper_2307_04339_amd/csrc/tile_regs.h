@@ -49,6 +49,13 @@ __device__ __forceinline__ void wait_and_meet_loads() {
     asm volatile("" ::: "memory");
 }
 
+// Wait for this wave's LDS operations.
+__device__ __forceinline__ void wait_lds() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8));
+    asm volatile("" ::: "memory");
+}
+
 // Raw epilogue parameters of TN channels from n0 into LDS at `lds` (bias, gamma, beta, mean, var,
 // TN floats each), by one wave; ordered like lds_dma16.
 template <int TN>

@@ -150,6 +150,60 @@ def test_batched_context_matches_oracle_and_is_elastic(ops, orc, dtype, B, H, S,
     _elastic(op, y, orc)
 
 
+# a single K chunk: the epilogue's parameters have one meeting between their writer and their readers.
+# M, N, K, 1x1 convolution stride (None: product), tile
+ONE_CHUNK = [
+    (4000, 120, 64, None, (64, 64)),
+    (4000, 120, 40, 2, (64, 64)),
+    (16000, 120, 64, None, (128, 64)),
+    (16000, 120, 40, 1, (128, 64)),
+]
+
+
+@pytest.mark.parametrize("case", ONE_CHUNK)
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_pipe_single_chunk_parameters(ops, orc, dtype, case):
+    M, N, K, stride, tile = case
+    rng = np.random.default_rng(12)
+    # parameters far apart from channel to channel: another channel's, or none, would show
+    b64 = (rng.uniform(-1, 1, N) + np.arange(N) % 7).astype(np.float32).astype(np.float64)
+    w, w64 = rand((N, K), dtype, seed=13, lo=-0.2, hi=0.2)
+    if stride is None:
+        x, x64 = rand((M, K), dtype, seed=14)
+        y = empty((M, N), dtype)
+        op = ops.gemm(x, w, y, bias=f32_dev(b64), act="none")
+        ref = orc.linear(x64, w64, bias=b64)
+    else:
+        x, x64 = rand((M // 400, 20 * stride, 20 * stride, K), dtype, seed=14)
+        y = empty((M // 400, 20, 20, N), dtype)
+        bn64 = np.stack([rng.uniform(0.5, 2, N), rng.uniform(-3, 3, N), rng.uniform(-1, 1, N),
+                         rng.uniform(0.5, 2, N)]).astype(np.float32).astype(np.float64)
+        op = ops.conv2d(x, w.reshape(N, 1, 1, K), y, stride=stride, pad=0, bias=f32_dev(b64), bn=f32_dev(bn64))
+        ref = orc.conv2d(x64, w64.reshape(N, 1, 1, K), stride=stride, pad=0, bias=b64, bn=tuple(bn64))
+    assert _is_pipe(op, tile), (op.info.path, op.info.tile_m, op.info.tile_n, op.info.lds_bytes)
+    op.run()
+    torch.cuda.synchronize()
+    assert rel_err(to_f64(y), ref) <= TOL[dtype]
+    _elastic(op, y, orc)
+
+
+@pytest.mark.parametrize("S", [40, 64])
+def test_context_of_a_single_chunk_matches_oracle(ops, orc, S):
+    B, H, D = 16, 12, 64
+    p, p64 = rand((B * H, S, S), "bf16", seed=15, lo=0.0, hi=1.0)
+    qkv, q64 = rand((B * S, 3 * H * D), "bf16", seed=16)
+    y = empty((B * S, H * D), "bf16")
+    op = ops.bgemm(p, qkv[:, 2 * H * D:], y, m=S, n=D, k=S, batch=B * H, batch_div=H, ldx=S, ldw=3 * H * D, ldy=H * D,
+                   sx=(H * S * S, S * S), sw=(S * 3 * H * D, D), sy=(S * H * D, D), b_nmajor=True)
+    assert _is_pipe(op, (64, 64)), (op.info.path, op.info.tile_m, op.info.tile_n, op.info.lds_bytes)
+    op.run()
+    torch.cuda.synchronize()
+    v = q64.reshape(B, S, 3, H, D)[:, :, 2]
+    ref = np.einsum("bhij,bjhd->bihd", p64.reshape(B, H, S, S), v).reshape(B * S, H * D)
+    assert rel_err(to_f64(y), ref) <= TOL["bf16"]
+    _elastic(op, y, orc)
+
+
 @pytest.mark.parametrize("n", [1, 3, 8, 77, 333, 512, 520, 2047, 2056])
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 def test_rows_of_any_length_match_oracle(ops, orc, dtype, n):
