@@ -382,14 +382,6 @@ __device__ __forceinline__ void ld_cols(const float *p, int64_t rem, float *out)
     }
 }
 
-// exp(x) of a softmax term, x <= 0: 16-bit results take the hardware's exp2 of x log2 e (about 1e-6
-// relative where the term is not negligible, against a rounding of 5e-4).
-template <class T>
-__device__ __forceinline__ float soft_exp(float x) {
-    if constexpr (sizeof(T) == 2) return __builtin_amdgcn_exp2f(x * 1.44269504088896340736f);
-    else return expf(x);
-}
-
 // Lane's values of a row: j = lane V + i 64 V (+ e), in increasing i.  Rows of up to kRowRegs vectors
 // per lane (2048 16-bit or 1024 fp32 values) are read from memory once and kept in registers for
 // every pass; longer rows are read again per pass.  The per-element operations are the same.
@@ -401,16 +393,37 @@ __device__ void softmax_row(const RowArgs &a, int64_t row, int lane) {
     T *yr = static_cast<T *>(a.y) + row * a.ldy;
     const int64_t j0 = (int64_t)lane * V;
     constexpr int64_t step = (int64_t)kWave * V;
-    // scaled values, -inf past the row's end
-    auto load = [&](int64_t j, float *v) {
-        ld_row_vec<T, V, RAG>(xr + j, a.n - j, 0.0f, v);
+    auto load = [&](int64_t j, float *v) { ld_row_vec<T, V, RAG>(xr + j, a.n - j, 0.0f, v); };
+    auto in_row = [&](int64_t j, int e) { return !RAG || j + e < a.n; };
+    auto most = [&](int64_t j, const float *v, float m) {
 #pragma unroll
-        for (int e = 0; e < V; ++e) v[e] = RAG && j + e >= a.n ? -INFINITY : a.scale * v[e];
+        for (int e = 0; e < V; ++e) m = in_row(j, e) ? fmaxf(m, a.scale * v[e]) : m;
+        return m;
     };
+    // exp(scale v - m), the difference in one rounding
+    auto term = [&](float v, float m) { return expf(__builtin_fmaf(a.scale, v, -m)); };
+    auto terms = [&](int64_t j, float *v, float m) {
+        float s = 0.0f;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            v[e] = term(v[e], m);
+            s += in_row(j, e) ? v[e] : 0.0f;
+        }
+        return s;
+    };
+    // v / s; 16-bit results: by the row's reciprocal and one correction, which gives the quotient's own
+    // rounding but for a few values next to a tie of fp32
     auto put = [&](int64_t j, const float *v, float s, float rs) {
         float o[V];
 #pragma unroll
-        for (int e = 0; e < V; ++e) o[e] = sizeof(T) == 2 ? v[e] * rs : v[e] / s;
+        for (int e = 0; e < V; ++e) {
+            if constexpr (sizeof(T) == 2) {
+                const float q = v[e] * rs;
+                o[e] = __builtin_fmaf(__builtin_fmaf(-q, s, v[e]), rs, q);
+            } else {
+                o[e] = v[e] / s;
+            }
+        }
         st_row_vec<T, V, RAG>(yr + j, a.n - j, o);
     };
     float m = -INFINITY, s = 0.0f;
@@ -421,20 +434,11 @@ __device__ void softmax_row(const RowArgs &a, int64_t row, int lane) {
             if (j0 + i * step < a.n) load(j0 + i * step, v[i]);
 #pragma unroll
         for (int i = 0; i < kRowRegs; ++i)
-            if (j0 + i * step < a.n) {
-#pragma unroll
-                for (int e = 0; e < V; ++e) m = fmaxf(m, v[i][e]);
-            }
+            if (j0 + i * step < a.n) m = most(j0 + i * step, v[i], m);
         m = wave_max(m);
 #pragma unroll
         for (int i = 0; i < kRowRegs; ++i)
-            if (j0 + i * step < a.n) {
-#pragma unroll
-                for (int e = 0; e < V; ++e) {
-                    v[i][e] = soft_exp<T>(v[i][e] - m);
-                    s += v[i][e];
-                }
-            }
+            if (j0 + i * step < a.n) s += terms(j0 + i * step, v[i], m);
         s = wave_sum(s);
         const float rs = 1.0f / s;
 #pragma unroll
@@ -445,21 +449,18 @@ __device__ void softmax_row(const RowArgs &a, int64_t row, int lane) {
     float v[V];
     for (int64_t j = j0; j < a.n; j += step) {
         load(j, v);
-#pragma unroll
-        for (int e = 0; e < V; ++e) m = fmaxf(m, v[e]);
+        m = most(j, v, m);
     }
     m = wave_max(m);
     for (int64_t j = j0; j < a.n; j += step) {
         load(j, v);
-#pragma unroll
-        for (int e = 0; e < V; ++e) s += soft_exp<T>(v[e] - m);
+        s += terms(j, v, m);
     }
     s = wave_sum(s);
     const float rs = 1.0f / s;
     for (int64_t j = j0; j < a.n; j += step) {
         load(j, v);
-#pragma unroll
-        for (int e = 0; e < V; ++e) v[e] = soft_exp<T>(v[e] - m);
+        terms(j, v, m);
         put(j, v, s, rs);
     }
 }
