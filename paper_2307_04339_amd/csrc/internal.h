@@ -37,7 +37,7 @@ int pipe_kernels_one_bf16(int cfg, const void *out[3], int *lds);
 int patch_kernels_f16(int cfg, const void *out[3], int *lds);
 int patch_kernels_bf16(int cfg, const void *out[3], int *lds);
 int pix_kernels(int dtype, int kind, bool vec, const void *out[3]);
-int row_kernels(int dtype, int kind, bool vec, const void *out[3]);
+int row_kernels(int dtype, int kind, int access, const void *out[3]);  // access: RowAccess
 int skinny_kernels(int dtype, int cg, const void *out[3]);  // cg: 16-column groups per tile (1 or 2)
 int skinny_group(int cg);                                   // K per wave group of that kernel
 // resident-weight direct convolution: (3x3, stride 1, C in {8,16,32,64}), (3x3, stride 2, C = 8),

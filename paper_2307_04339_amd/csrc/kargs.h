@@ -128,6 +128,9 @@ struct RowArgs {
 enum PixKind { PIX_DW = 0, PIX_MAX = 1, PIX_AVG = 2, PIX_EW = 3, PIX_DW3 = 4 };
 constexpr int kDwStrip = 4;  // PIX_DW3: output pixels along a row per lane item
 enum RowKind { ROW_SOFTMAX = 0, ROW_LAYERNORM = 1 };
+// how a row is read: whole 16-byte vectors, 16-byte pieces at any alignment with the last by element, elements
+enum RowAccess { ROWS_VEC = 0, ROWS_RAGGED = 1, ROWS_ELEMENT = 2 };
+constexpr int kShortRow = 512;  // values of a row up to which reading by element keeps it in registers
 enum IgemmLayout { LAY_VEC = 0, LAY_SCALAR = 1, LAY_VEC_NB = 2, LAY_SCALAR_NB = 3, LAY_VEC_UNI = 4, LAY_HALO = 5, LAY_RW = 6, LAY_PATCH = 7, LAY_PIPE = 8, LAY_RAG_NB = 9, LAY_PIPE_NB = 10 };
 enum IgemmCfg { CFG_32 = 1, CFG_64 = 2, CFG_128 = 3, CFG_128x64 = 4, CFG_256x128 = 6, CFG_HALO = 7, CFG_RW = 8,
                 // library choice only (no descriptor code): 3x3 stride-1 patch kernel, 256 pixels x 128 / 64 channels

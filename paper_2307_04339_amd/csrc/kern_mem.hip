@@ -46,31 +46,34 @@ int pix_kernels(int dtype, int kind, bool vec, const void *out[3]) {
     }
 }
 
-template <class T, int KIND, bool RAG>
+template <class T, int V, int KIND, bool RAG>
 static void row_table(const void *out[3]) {
-    constexpr int V = 16 / sizeof(T);
     out[0] = reinterpret_cast<const void *>(&row_kernel<T, V, KIND, 1, RAG>);
     out[1] = reinterpret_cast<const void *>(&row_kernel<T, V, KIND, 2, RAG>);
     out[2] = reinterpret_cast<const void *>(&row_kernel<T, V, KIND, 4, RAG>);
 }
 
-// vec: rows of whole 16-byte vectors at 16-byte addresses; otherwise any length and alignment
-template <class T>
-static int row_table_k(int kind, bool vec, const void *out[3]) {
-    switch (kind * 2 + (vec ? 1 : 0)) {
-    case 0: row_table<T, ROW_SOFTMAX, true>(out); return 0;
-    case 1: row_table<T, ROW_SOFTMAX, false>(out); return 0;
-    case 2: row_table<T, ROW_LAYERNORM, true>(out); return 0;
-    case 3: row_table<T, ROW_LAYERNORM, false>(out); return 0;
+template <class T, int KIND>
+static int row_table_k(int access, const void *out[3]) {
+    constexpr int V = 16 / sizeof(T);
+    switch (access) {
+    case ROWS_VEC: row_table<T, V, KIND, false>(out); return 0;
+    case ROWS_RAGGED: row_table<T, V, KIND, true>(out); return 0;
+    case ROWS_ELEMENT: row_table<T, 1, KIND, false>(out); return 0;
     default: return -1;
     }
 }
 
-int row_kernels(int dtype, int kind, bool vec, const void *out[3]) {
+template <class T>
+static int row_table_t(int kind, int access, const void *out[3]) {
+    return kind == ROW_SOFTMAX ? row_table_k<T, ROW_SOFTMAX>(access, out) : row_table_k<T, ROW_LAYERNORM>(access, out);
+}
+
+int row_kernels(int dtype, int kind, int access, const void *out[3]) {
     switch (dtype) {
-    case 0: return row_table_k<float>(kind, vec, out);
-    case 1: return row_table_k<half_t>(kind, vec, out);
-    case 2: return row_table_k<bf16_t>(kind, vec, out);
+    case 0: return row_table_t<float>(kind, access, out);
+    case 1: return row_table_t<half_t>(kind, access, out);
+    case 2: return row_table_t<bf16_t>(kind, access, out);
     default: return -1;
     }
 }

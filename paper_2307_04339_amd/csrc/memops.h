@@ -301,12 +301,11 @@ __global__ __launch_bounds__(kWave * P) void pix_kernel(PixArgs a, Shard sh) {
 }
 
 // ------------------------------------------------------------------- rows
-// What bounded the row kernels was issue, not memory: 49152 rows of 512 bf16 softmax values took
-// 27.8 us for 100 MB, of which a full expf and an IEEE division per value were most, and twelve LDS
-// permutes per row the rest.  Reductions now combine lanes with DPP moves and lane swaps in a fixed
-// order; 16-bit results take one reciprocal per row and the hardware exponential: 17 us, 5.9 TB/s.
-// Rows of any length and alignment are read in 16-byte pieces too (2 x 8 x 333 rows of 333: 7.6 ->
-// 6.5 us), the last piece of a row by element.
+// What bounds the row kernels is issue, not memory: 49152 rows of 512 bf16 softmax values took 25.6 us
+// for 100 MB, twelve LDS permutes per row and an IEEE division per value among it.  Reductions now
+// combine lanes with DPP moves and lane swaps in a fixed order, and 16-bit results multiply by the row's
+// reciprocal and correct once: 22.4 us, 4.5 TB/s; the rest is the exponential.  Rows that are no whole
+// 16-byte vectors: by element up to kShortRow values, in 16-byte pieces beyond, the last piece by element.
 
 // Sum / maximum over the wave, the same on every lane: lanes 1, 2, 4 and 8 apart by DPP (quad_perm,
 // row_half_mirror, row_mirror), 16 and 32 apart by lane swaps.
@@ -335,10 +334,12 @@ __device__ __forceinline__ float wave_max(float v) {
 }
 
 // V consecutive values of a row, `rem` of which exist (the others read `fill`); RAG: rows of any
-// length and alignment.
+// length and alignment.  V = 1: any alignment, one value.
 template <class T, int V, bool RAG>
 __device__ __forceinline__ void ld_row_vec(const T *p, int64_t rem, float fill, float *out) {
-    if (!RAG || rem >= V) {
+    if constexpr (V == 1) {
+        out[0] = ld_f(p);
+    } else if (!RAG || rem >= V) {
         Vec16<T> vv;
         if constexpr (RAG) vv.u = reinterpret_cast<const Loose16 *>(p)->u;
         else vv = ld_vec(p);
@@ -354,7 +355,9 @@ __device__ __forceinline__ void ld_row_vec(const T *p, int64_t rem, float fill, 
 }
 template <class T, int V, bool RAG>
 __device__ __forceinline__ void st_row_vec(T *p, int64_t rem, const float *v) {
-    if (!RAG || rem >= V) {
+    if constexpr (V == 1) {
+        st_f(p, v[0]);
+    } else if (!RAG || rem >= V) {
         Vec16<T> o;
 #pragma unroll
         for (int e = 0; e < V; ++e) o.e[e] = TypeOps<T>::from_f(v[e]);
@@ -369,7 +372,9 @@ __device__ __forceinline__ void st_row_vec(T *p, int64_t rem, const float *v) {
 // V floats of a per-column vector, `rem` of which exist
 template <int V, bool RAG>
 __device__ __forceinline__ void ld_cols(const float *p, int64_t rem, float *out) {
-    if (!RAG || rem >= V) {
+    if constexpr (V == 1) {
+        out[0] = p[0];
+    } else if (!RAG || rem >= V) {
 #pragma unroll
         for (int q = 0; q < V / 4; ++q) {
             const f32x4 f = reinterpret_cast<const Loose16f *>(p + 4 * q)->f;
@@ -383,9 +388,10 @@ __device__ __forceinline__ void ld_cols(const float *p, int64_t rem, float *out)
 }
 
 // Lane's values of a row: j = lane V + i 64 V (+ e), in increasing i.  Rows of up to kRowRegs vectors
-// per lane (2048 16-bit or 1024 fp32 values) are read from memory once and kept in registers for
-// every pass; longer rows are read again per pass.  The per-element operations are the same.
-constexpr int kRowRegs = 4;
+// per lane (2048 16-bit or 1024 fp32 values, kShortRow by element) are read from memory once and kept in
+// registers for every pass; longer rows are read again per pass.  The per-element operations are the same.
+template <int V>
+constexpr int kRowRegs = V == 1 ? kShortRow / kWave : 4;
 
 template <class T, int V, bool RAG>
 __device__ void softmax_row(const RowArgs &a, int64_t row, int lane) {
@@ -427,25 +433,31 @@ __device__ void softmax_row(const RowArgs &a, int64_t row, int lane) {
         st_row_vec<T, V, RAG>(yr + j, a.n - j, o);
     };
     float m = -INFINITY, s = 0.0f;
-    if (a.n <= kRowRegs * step) {
-        float v[kRowRegs][V];
+    auto in_registers = [&](auto regs) {
+        constexpr int NR = decltype(regs)::value;
+        float v[NR][V];
 #pragma unroll
-        for (int i = 0; i < kRowRegs; ++i)
+        for (int i = 0; i < NR; ++i)
             if (j0 + i * step < a.n) load(j0 + i * step, v[i]);
 #pragma unroll
-        for (int i = 0; i < kRowRegs; ++i)
+        for (int i = 0; i < NR; ++i)
             if (j0 + i * step < a.n) m = most(j0 + i * step, v[i], m);
         m = wave_max(m);
 #pragma unroll
-        for (int i = 0; i < kRowRegs; ++i)
+        for (int i = 0; i < NR; ++i)
             if (j0 + i * step < a.n) s += terms(j0 + i * step, v[i], m);
         s = wave_sum(s);
         const float rs = 1.0f / s;
 #pragma unroll
-        for (int i = 0; i < kRowRegs; ++i)
+        for (int i = 0; i < NR; ++i)
             if (j0 + i * step < a.n) put(j0 + i * step, v[i], s, rs);
-        return;
+    };
+    if constexpr (V == 1) {
+        // by element, the tests of whether a value exists outweigh the work of a short row
+        if (a.n <= 2 * step) return in_registers(ActTag<2>{});
+        if (a.n <= 4 * step) return in_registers(ActTag<4>{});
     }
+    if (a.n <= kRowRegs<V> * step) return in_registers(ActTag<kRowRegs<V>>{});
     float v[V];
     for (int64_t j = j0; j < a.n; j += step) {
         load(j, v);
@@ -495,13 +507,13 @@ __device__ void layernorm_row(const RowArgs &a, int64_t row, int lane) {
         st_row_vec<T, V, RAG>(yr + j, a.n - j, v);
     };
     float s = 0.0f, q = 0.0f;
-    if (a.n <= kRowRegs * step) {
+    if (a.n <= kRowRegs<V> * step) {
         // the row and the column parameters of its first kColRegs vectors per lane are requested
         // before the first reduction (of all of them, the registers would halve the waves in flight)
-        constexpr int kColRegs = 2;
-        float v[kRowRegs][V], g[kColRegs][V], b[kColRegs][V];
+        constexpr int kColRegs = V == 1 ? kRowRegs<V> : 2;
+        float v[kRowRegs<V>][V], g[kColRegs][V], b[kColRegs][V];
 #pragma unroll
-        for (int i = 0; i < kRowRegs; ++i) {
+        for (int i = 0; i < kRowRegs<V>; ++i) {
             const int64_t j = j0 + i * step;
             if (j < a.n) {
                 load(j, v[i]);
@@ -512,18 +524,18 @@ __device__ void layernorm_row(const RowArgs &a, int64_t row, int lane) {
             }
         }
 #pragma unroll
-        for (int i = 0; i < kRowRegs; ++i)
+        for (int i = 0; i < kRowRegs<V>; ++i)
             if (j0 + i * step < a.n) {
 #pragma unroll
                 for (int e = 0; e < V; ++e) s += v[i][e];
             }
         const float mean = wave_sum(s) / (float)a.n;
 #pragma unroll
-        for (int i = 0; i < kRowRegs; ++i)
+        for (int i = 0; i < kRowRegs<V>; ++i)
             if (j0 + i * step < a.n) q += square(j0 + i * step, v[i], mean);
         const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)a.n + a.eps);
 #pragma unroll
-        for (int i = 0; i < kRowRegs; ++i) {
+        for (int i = 0; i < kRowRegs<V>; ++i) {
             const int64_t j = j0 + i * step;
             if (j < a.n) {
                 if (i < kColRegs) {

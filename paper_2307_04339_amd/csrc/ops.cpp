@@ -791,7 +791,13 @@ static int create_row(miriam_op *op) {
                      aligned16(d.y) && (!a.has_res || aligned16(d.residual));
     op->T = cdiv(a.rows, 4);
     op->lds_bytes = 0;
-    if (row_kernels(d.dtype, kind, vec, op->kern) != 0) return einval("no kernel for this dtype");
+    // Rows that are no whole vectors: by element where that keeps them in registers (all lanes at work, no
+    // value past the row's end), else in 16-byte pieces.  4 million bf16 values, pieces / elements, us:
+    // softmax of rows of 82 39.4 / 13.7, of 255 15.7 / 7.4, of 511 9.6 / 6.7; layer norm with residual of
+    // rows of 123 53.4 / 12.2, of 511 15.8 / 7.6.  Longer rows, re-read per pass by element: layer norm
+    // of rows of 769 14.5 / 14.9, of 1001 11.0 / 16.7.
+    const int access = vec ? ROWS_VEC : a.n <= kShortRow ? ROWS_ELEMENT : ROWS_RAGGED;
+    if (row_kernels(d.dtype, kind, access, op->kern) != 0) return einval("no kernel for this dtype");
     const double n = (double)a.rows * a.n;
     op->flops = 5.0 * n;
     op->bytes = es * (n * 2.0 + (a.has_res ? n : 0.0)) + (kind == ROW_LAYERNORM ? 8.0 * a.n : 0.0);
