@@ -227,6 +227,10 @@ static int choose_pipe(const miriam_op_desc &d, const IgemmArgs &a, int64_t batc
 //    50..56 tiles lose, 8x28x28x128->128 9.4 -> 10.0, 2x28x28x256->512 14.2 -> 14.7: a tile's K loop
 //    is then the whole time.  Where C is no multiple of 64 the implicit GEMM decodes K per lane, and
 //    3/16 suffice: 51 tiles 3x37x37x96->160 12.1 -> 8.6.
+//  - tiles at least half full where they end with an image: 128x4x4x512->512, 16 of 256 pixels, 21.4
+//    (implicit GEMM) / 98.7, 128x1x64x256->256, a quarter, 19.3 / 29.6; 128x2x70x256->256, 55%, 41.0 / 31.7.
+//    With two chunks or less and more than two rounds nine tenths: 128x3x100x64->512, 59%, 36.5 / 43.2,
+//    128x5x104x64->512, 68%, 60.2 / 65.3, 64x7x160x64->512, 88%, 62.8 / 71.2; full, 8x120x120x64->512, 99.5 / 93.5.
 //  - `narrow` (the resident-weight or the LDS-patch kernel would serve the layer): only up to one
 //    tile per CU.  16x56x56x64->64 (196 tiles) 13.6 -> 8.7, 8x90x90x64->64 (256) 18.9 -> 10.3;
 //    8x224x224x64->64 (1568) 41.9 -> 55.0, its weights streaming again for every tile.
@@ -257,8 +261,9 @@ static int choose_patch(const miriam_op_desc &d, const IgemmArgs &a, bool vec, b
         *group = howo;
     }
     if (run > kPatchPixelsW) return 0;
-    const int64_t cus = device_cus(), t64 = a.M / *group * cdiv(*group, 256) * cdiv(a.Nc, 64);
+    const int64_t cus = device_cus(), padded = cdiv(*group, 256) * 256, t64 = a.M / *group * (padded / 256) * cdiv(a.Nc, 64);
     if (t64 * (d.c % 64 == 0 ? 8 : 16) < cus * 3) return 0;
+    if (*group * 2 < padded || (d.c <= 64 && t64 > 2 * cus && *group * 10 < padded * 9)) return 0;
     if (narrow && t64 > cus) return 0;
     if (run > kPatchPixels) return CFG_PATCH_64W;
     return a.Nc > 64 && t64 > 2 * cus ? CFG_PATCH_128 : CFG_PATCH_64;
