@@ -178,32 +178,48 @@ static int pipe_tile_n(int cfg) {
 }
 
 // Register-tile pipelined contraction (gemm_pipe.h) for fp16 / bf16 with whole 16-byte output pieces
-// and 32-bit offsets per batch entry: CFG_PIPE_*, or 0 where igemm_dma_kernel stays.  The tile with
-// the least estimated time: rounds of tiles over the CUs x (K chunks x the chunk's time + the rest of
-// a tile's), in ns, fitted to a sweep of products and convolutions (one workgroup per CU; a 64x64
-// chunk takes 220 ns, a 256x192 one 1350 on the whole chip: the load path's 33 bytes per clock and
-// CU).  Measured back to back in a captured graph, bf16, igemm_dma_kernel -> this: 4096x2304x768 28.9
-// -> 23.3 us (256x192), 4096x768x3072 31.7 -> 26.3 (128x128), 2048x2304x768 20.7 -> 16.2 (256x128),
-// 2048x768x3072 22.0 -> 19.0 (128x64), 8x56x56x128->256 3x3/2 12.7 -> 10.9 (128x64), 16x7x7x160->960
-// 1x1 6.7 -> 4.8 (64x64).  [k][n] right operands (attention's P V, bf16, from the register-staged
-// kernel): 96 x 512x64x512 19.0 -> 14.6 us (256x64), 48 x 256x64x256 7.0 -> 5.1 (64x64).  Few small tiles with long K stay there, where it splits K or takes 32x32
-// tiles: 104 tiles of 1x28x28x256->512 12.0 against 12.8, 200 tiles of 8x14x14x512->512 20.4 (two
-// slices) against 22.9; up to 12 chunks the line is a quarter of the CUs, 72 tiles of 128x2304x768
-// 6.7 -> 6.6, 49 of 16x14x14x384->64 4.8 against 5.3.
-static int choose_pipe(const miriam_op_desc &d, const IgemmArgs &a, int64_t batch, bool nmaj) {
+// and 32-bit offsets per batch entry: CFG_PIPE_*, or 0 where igemm_dma_kernel stays, which would take
+// tile `other`.  The tile with the least estimated time: rounds of tiles over the CUs x (K chunks x the
+// chunk's time + the rest of a tile's), in ns, fitted to a sweep of products and convolutions (one
+// workgroup per CU; a 64x64 chunk takes 220 ns, a 256x192 one 1350 on the whole chip: the load path's
+// 33 bytes per clock and CU).  Measured back to back in a captured graph, bf16, igemm_dma_kernel -> this:
+// 4096x2304x768 28.9 -> 23.3 us (256x192), 4096x768x3072 31.7 -> 26.3 (128x128), 2048x2304x768 20.7 ->
+// 16.2 (256x128), 2048x768x3072 22.0 -> 19.0 (128x64), 8x56x56x128->256 3x3/2 12.7 -> 10.9 (128x64),
+// 16x7x7x160->960 1x1 6.7 -> 4.8 (64x64).  [k][n] right operands (attention's P V, bf16, from the
+// register-staged kernel): 96 x 512x64x512 19.0 -> 14.6 us (256x64), 48 x 256x64x256 7.0 -> 5.1 (64x64).
+//
+// igemm_dma_kernel stays, from sweeps of 475 and 144 shapes (its time / this kernel's, us):
+//  - where it takes 32x32 tiles and whole K chunks, one tile per CU at most: 1x76x76x64->160 3x3/2 (230
+//    tiles) 5.4 / 6.5, 500x512x512 (256) 4.8 / 5.5, 1000x256x64 (256) 3.7 / 4.0 (K = 40, decoded per lane,
+//    3.9 / 3.9); or two per CU and more than 12 chunks (8 with several taps): 1000x512x3072 (512 tiles,
+//    48 chunks) 12.8 / 14.9, 10000x24x2048 (313, 32) 10.2 / 12.4, 2000x256x1024 (504, 16) 7.1 / 7.4, but
+//    128x2304x768 (288, 12) 6.5 / 6.5, 2000x256x512 (504, 8) 5.8 / 5.6, 4100x64x192 (258, 3) 4.5 / 4.5,
+//    6x62x62x320->96 3x3/2 (543, 45) 15.4 / 15.1.
+//  - where it takes 128x64 tiles and this kernel would take as many, more than one per CU: two of its
+//    workgroups share a CU.  20x50x50x192->64 1x1 (391 tiles) 7.8 / 9.0, 44x50x50x320->24 (860) 16.6 / 21.4,
+//    13x28x111x192->24 5x5 (316) 42.9 / 50.5, 14x100x100x64->24 3x3/2 (274) 10.2 / 12.8; 215 tiles 8.9 / 7.6.
+//    Up to three per CU not where C is no multiple of 64, and it decodes K per lane: 32x50x50x144->24
+//    (625) 15.4 / 11.3, 25x50x50x96->64 (489) 8.8 / 9.0; 44x50x50x144->64 (860) 16.5 / 19.7.
+//  - few 64x64 tiles with long K, where it splits K: 200 tiles of 8x14x14x512->512 20.4 (two slices) / 22.9;
+//    fewer than a quarter of the CUs' 64x64 tiles, or half beyond 12 chunks: 49 of 16x14x14x384->64 4.8 / 5.3.
+static int choose_pipe(const miriam_op_desc &d, const IgemmArgs &a, int64_t batch, bool nmaj, int other) {
     const int64_t es = esize(d.dtype), lim = (int64_t)1 << 31, kt = 128 / es;
     const bool taps = a.KH * a.KW > 1;
     if (d.dtype == MIRIAM_F32 || !a.vec_store || a.Nc % 8 != 0 || (taps && a.C % kt != 0)) return 0;
     if ((d.kind == MIRIAM_OP_CONV2D ? d.n * a.img_x : (a.M - 1) * a.ldx + a.K) * es >= lim ||
         (nmaj ? (a.K - 1) * a.ldw + a.Nc : (a.Nc - 1) * a.ldw + a.K) * es >= lim || ((a.M - 1) * a.ldy + a.Nc) * es >= lim)
         return 0;
-    const int64_t cus = device_cus(), nch = cdiv(a.K, kt), t64 = batch * cdiv(a.M, 64) * cdiv(a.Nc, 64);
-    if (t64 * (nch <= 12 ? 4 : 2) < cus) return 0;
+    const int64_t cus = device_cus(), nch = cdiv(a.K, kt);
+    if (batch * cdiv(a.M, 64) * cdiv(a.Nc, 64) * (nch <= 12 ? 4 : 2) < cus) return 0;
+    if (!nmaj && other == CFG_32 && a.C % kt == 0) {
+        const int64_t t32 = batch * cdiv(a.M, 32) * cdiv(a.Nc, 32);
+        if (t32 <= cus || (t32 <= 2 * cus && nch > (taps ? 8 : 12))) return 0;
+    }
     struct Cost { int cfg; int64_t chunk, rest; };
     static const Cost costs[6] = {{CFG_PIPE_64, 220, 1800}, {CFG_PIPE_128x64, 276, 2500}, {CFG_PIPE_128, 420, 3500},
                                   {CFG_PIPE_256x128, 830, 4500}, {CFG_PIPE_256x192, 1350, 6000}, {CFG_PIPE_256x64, 460, 3500}};
     int best = 0;
-    int64_t least = INT64_MAX;
+    int64_t least = INT64_MAX, best_tiles = 0;
     for (const Cost &c : costs) {
         if (taps && c.cfg == CFG_PIPE_256x192) continue;
         if (nmaj ? pipe_tile_n(c.cfg) != 64 : c.cfg == CFG_PIPE_256x64) continue;
@@ -212,9 +228,10 @@ static int choose_pipe(const miriam_op_desc &d, const IgemmArgs &a, int64_t batc
         if (ns < least) {
             least = ns;
             best = c.cfg;
+            best_tiles = tiles;
         }
     }
-    // long K on few small tiles: igemm_dma_kernel splits K there
+    if (!nmaj && best == CFG_PIPE_128x64 && other == CFG_128x64 && best_tiles > (a.C % kt == 0 ? 1 : 3) * cus) return 0;
     return best == CFG_PIPE_64 && nch >= 64 ? 0 : best;
 }
 
@@ -464,7 +481,7 @@ static int create_igemm(miriam_op *op) {
     if (cfg == 0 && halo_fits) cfg = CFG_HALO;
     if (cfg == 0) cfg = (skinny_ok && !memidx) ? TILE_SKINNY : choose_cfg(batch, a.M, a.Nc, cdiv(a.K * es, 128));
     if (d.tile == 0 && !memidx && a_vec && b_vec && d.ksplit <= 1 && cfg >= CFG_32 && cfg <= CFG_128x64) {
-        pipe = choose_pipe(d, a, batch, nmaj);
+        pipe = choose_pipe(d, a, batch, nmaj, cfg);
         if (pipe) cfg = pipe;
     }
     if (memidx && (cfg == CFG_RW || cfg == CFG_HALO || cfg == TILE_SKINNY))

@@ -75,7 +75,8 @@ def test_pipe_gemm_matches_oracle_and_is_elastic(ops, orc, dtype, case):
 
 # N, H, W, C, K, ks, stride, pad, act, bn, residual, tile
 CONVS = [
-    (2, 40, 40, 64, 264, 3, 2, 1, "relu", True, False, (64, 64)),
+    # (five images: with two its 225 32x32 tiles fit the CUs one each, and it runs on those)
+    (5, 40, 40, 64, 264, 3, 2, 1, "relu", True, False, (64, 64)),
     (9, 21, 23, 144, 24, 1, 1, 0, "none", True, True, (64, 64)),     # one tap, K tail of 16, narrow output
     (9, 41, 23, 40, 72, 1, 2, 0, "relu6", False, False, (64, 64)),   # one tap, stride 2, K below a chunk
     (15, 40, 40, 64, 136, 3, 2, 1, "relu", False, True, (128, 64)),

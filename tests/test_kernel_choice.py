@@ -38,3 +38,32 @@ PATCH_LDS = [2 * pixels * 64 + 9 * tn * 64 + 28 * tn for pixels, tn in [(512, 64
 def test_patch_kernel_needs_full_tiles(n, h, w, c, k, patch):
     tm, _, lds = conv(n, h, w, c, k, 3)
     assert (tm == 256 and lds in PATCH_LDS) == patch
+
+
+def pipe_lds(tm, tn):
+    """LDS of the register-tile pipeline: up to five stages of a 128-byte K chunk, 28 bytes per column."""
+    stage = (tm + tn) * 128
+    return min(5, ((160 if stage >= 24 * 1024 else 80) * 1024 - 28 * tn) // stage) * stage + 28 * tn
+
+
+def is_pipe(tm, tn, lds):
+    return lds == pipe_lds(tm, tn)
+
+
+@pytest.mark.parametrize("m,n,k,pipe", [
+    (500, 512, 512, False), (200, 1024, 256, False), (1000, 512, 3072, False), (10000, 24, 2048, False),
+    (2000, 256, 1024, False), (2000, 256, 512, True), (128, 2304, 768, True), (10000, 160, 3072, True),
+    (50000, 64, 192, False), (40000, 64, 3072, False), (25000, 64, 3072, True), (50000, 64, 144, True),
+    (110000, 64, 144, False), (4096, 2304, 768, True),
+])
+def test_pipeline_needs_rounds_for_products(m, n, k, pipe):
+    assert is_pipe(*tile_of(kind=L.OP_GEMM, dtype=L.BF16, m=m, nn=n, kk=k)) == pipe
+
+
+@pytest.mark.parametrize("n,h,w,c,k,ks,stride,pipe", [
+    (1, 76, 76, 64, 160, 3, 2, False), (1, 96, 114, 320, 160, 3, 2, False), (13, 28, 111, 192, 24, 5, 1, False),
+    (14, 100, 100, 64, 24, 3, 2, False), (11, 100, 100, 64, 24, 3, 2, True), (8, 56, 56, 128, 256, 3, 2, True),
+    (44, 50, 50, 320, 24, 1, 1, False), (32, 50, 50, 144, 24, 1, 1, True),
+])
+def test_pipeline_needs_rounds_for_convolutions(n, h, w, c, k, ks, stride, pipe):
+    assert is_pipe(*conv(n, h, w, c, k, ks, stride)) == pipe
