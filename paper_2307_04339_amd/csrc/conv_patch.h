@@ -52,6 +52,16 @@ struct PatchKernel {
     static constexpr int WN = kLogicalWaves / WM;         // logical waves: WM along pixels, WN along channels
     static constexpr int BP = TM / WM / 32, BC = TN / WN / 32;  // MFMA blocks of a logical wave
     static constexpr int NT = kWave * P;
+    // smaller physical blocks: a wave holds SL logical waves at once (16 MFMA blocks, half of its registers),
+    // SM of them along the pixels times SN along the channels; the remaining ones in further rounds, each of
+    // which loads the tile's operands again.  8x28x28x512->512 in blocks of 128 / 64: one at a time 52.1 / 119.7
+    // us, eight blocks 44.0 / 91.2, sixteen (with up to 69 spills in blocks of 64) 44.1 / 81.6 (igemm_dma_kernel
+    // 51.6 / 107.5)
+    static constexpr int FIT = 16 / (BP * BC);
+    static constexpr int SL = kLogicalWaves / P < FIT ? kLogicalWaves / P : FIT;
+    static constexpr int SN = P == 1 && WN == 2 && SL > 1 ? 2 : 1, SM = SL / SN;
+    static constexpr int MSTEP = SN * P / WN > 0 ? SN * P / WN : 1;  // logical rows between a wave's pixel slots
+    static constexpr int RB = SM * BP, CB = SN * BC;      // MFMA blocks of a physical wave
     static constexpr int KC = 32;                         // channels per chunk (64-byte rows)
     static constexpr int PATCH = NPX * 64;
     static constexpr int NPW = NPX / 16 / P;              // patch loads per wave (16 pixels each)
@@ -63,7 +73,7 @@ struct PatchKernel {
     static constexpr int RAW0 = W0 + 3 * BSTAGE;
     static constexpr int AFF0 = RAW0 + 5 * TN * 4;
     static constexpr int LDS_BYTES = AFF0 + 2 * TN * 4;
-    static constexpr int ROUNDS = kLogicalWaves / P;
+    static constexpr int ROUNDS = kLogicalWaves / P / SL;
     static constexpr int NST = BP * BC * 2;               // output stores per wave and tile
     static_assert(NPX % (16 * P) == 0 && TN % (16 * P) == 0, "load instructions must divide evenly");
     static_assert(NB + PART + (P == 4 ? NST : 0) < 64, "vmcnt range");
@@ -76,9 +86,9 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
     typedef typename K_::MF MF;
     typedef typename MF::op_t op_t;
     typedef typename MF::acc_t acc_t;
-    constexpr int WN = K_::WN, BP = K_::BP, BC = K_::BC, NPW = K_::NPW, PART = K_::PART, RG = K_::RG, NB = K_::NB;
+    constexpr int WN = K_::WN, BP = K_::BP, RB = K_::RB, CB = K_::CB, SL = K_::SL, NPW = K_::NPW, PART = K_::PART, RG = K_::RG, NB = K_::NB;
     constexpr int NST = K_::NST, ROUNDS = K_::ROUNDS;
-    constexpr int NM = BP * BC, NOP = BP + BC;            // MFMAs and operand reads per k-step
+    constexpr int NM = RB * CB, NOP = RB + CB;            // MFMAs and operand reads per k-step
     constexpr int NL = PART + NB, HEAD = PART < NM ? PART : NM;  // loads per step; of them under its last k-step
 
     __shared__ __attribute__((aligned(1024))) char smem_[K_::LDS_BYTES];
@@ -120,8 +130,10 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
     // ---- the unit (tile, round) being loaded
     uint32_t voff_p[NPW];   // byte offset of this lane's piece of each patch load, channel 0 (or out of range)
     uint32_t voff_w[RG];    // byte offset of this lane's piece of each weight row group, tap 0, channel 0
-    uint32_t pxb[BP];       // LDS row of each block's operand pixel for tap (0, 0), with this lane's half
+    uint32_t pxb[RB];       // LDS row of each block's operand pixel for tap (0, 0), with this lane's half
     uint32_t m0 = 0, n0 = 0, mlast = 0;  // first pixel and channel, last pixel
+    // pixel of the tile, from the wave's first, at which block b starts
+    auto block_row = [](int b) { return (b / BP) * K_::MSTEP * (TM / WM) + (b % BP) * 32; };
     auto decode = [&](const TileDigits<3> &d, int rd) {
         const uint32_t g0 = d.d[2] * group;
         m0 = g0 + d.d[1] * (uint32_t)TM;
@@ -144,10 +156,10 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
             const uint32_t n = n0 + (uint32_t)(16 * (j * P + pw) + (lane >> 2));
             voff_w[j] = n < Nc32 ? (n * (uint32_t)a.ldw + (uint32_t)piece_ * 8u) * 2u : kOutOfRange;
         }
-        const int lam = rd * P + pw, wm = lam / WN;
+        const int wm = (rd * SL * P + pw) / WN;
 #pragma unroll
-        for (int b = 0; b < BP; ++b) {
-            const uint32_t m = m0 + (uint32_t)(wm * (TM / WM) + b * 32 + xl);
+        for (int b = 0; b < RB; ++b) {
+            const uint32_t m = m0 + (uint32_t)(wm * (TM / WM) + block_row(b) + xl);
             pxb[b] = ((lin_of(m <= last ? m : last) - L0) << 6) | ((uint32_t)hx << 4);
         }
     };
@@ -204,11 +216,12 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
 
         // ---- epilogue of round rd from registers: v = acc * sc + sh, + residual, activation,
         // one rounding, 16-byte stores
-        auto epilogue = [&](int rd, acc_t (&acc)[BP][BC]) {
-            const int lam = rd * P + pw, wm = lam / WN, wn = lam % WN;
-            trace_wave(sh, t, lam, pw, rd);
+        auto epilogue = [&](int rd, acc_t (&acc)[RB][CB]) {
+            const int lam = rd * SL * P + pw, wm = lam / WN, wn = lam % WN;  // the round's first slot
+#pragma unroll
+            for (int sl = 0; sl < SL; ++sl) trace_wave(sh, t, lam + sl * P, pw, rd * SL + sl);
             finish_tile<T>(a.epi, smem + K_::AFF0, TN, wn * (TN / WN), tn0, Nc32, ry, rr, acc, [&](int b, int x, uint32_t &row) {
-                const uint32_t m = tm0 + (uint32_t)(wm * (TM / WM) + b * 32 + x);
+                const uint32_t m = tm0 + (uint32_t)(wm * (TM / WM) + block_row(b) + x);
                 row = m * (uint32_t)a.ldy;
                 return m <= tlast;
             });
@@ -216,7 +229,7 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
 
 #pragma unroll 1
         for (int rd = 0; rd < ROUNDS; ++rd) {
-            acc_t acc[BP][BC];
+            acc_t acc[RB][CB];
             if (!loaded) {
                 decode(td, rd);
                 prologue();
@@ -229,17 +242,17 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
             tm0 = m0;
             tn0 = n0;
             tlast = mlast;
-            const int wn = (rd * P + pw) % WN;
+            const int wn = (rd * SL * P + pw) % WN;
 #pragma unroll
-            for (int b = 0; b < BP; ++b)
+            for (int b = 0; b < RB; ++b)
 #pragma unroll
-                for (int c = 0; c < BC; ++c) acc[b][c] = acc_t{};
+                for (int c = 0; c < CB; ++c) acc[b][c] = acc_t{};
 
-            op_t xo[2][BP], wo[2][BC];
+            op_t xo[2][RB], wo[2][CB];
             // LDS addresses of the pixels of a tap: row px at 64 px, piece hx (the halves of a k-step
             // pair differ in bit 5) swizzled by px bits 2 and 3.  Taps of a filter row take the sets
             // 0, 1, 2 in turn; the next tap's are computed under the MFMAs of the current one.
-            uint32_t ad[3][BP];
+            uint32_t ad[3][RB];
             const uint32_t hx4 = (uint32_t)hx << 4;
             const uint32_t wbase = (uint32_t)K_::W0 + (uint32_t)(wn * (TN / WN) + xl) * 64u + (hx4 ^ ((uint32_t)(xl << 2) & 0x30u));
             auto tap_offset = [&](int r, int s, uint32_t pb) -> uint32_t { return pb + (((uint32_t)r * PW + (uint32_t)s) << 6); };
@@ -248,17 +261,17 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
                 ad[set][b] = row ^ ((row >> 4) & 0x30u);
             };
 
-            // operand i of half kk of tap (r, s): the BC channel blocks, then the BP pixel blocks (at
+            // operand i of half kk of tap (r, s): the channel blocks, then the pixel blocks (at
             // the tap's addresses)
             auto fetch1 = [&](int i, int r, int s, int kk, int set) {
-                if (i < BC)
+                if (i < CB)
                     wo[set][i] = *reinterpret_cast<const op_t *>(smem + (wbase ^ (uint32_t)(kk << 5)) + r * K_::BSTAGE + s * TN * 64 + i * 2048);
                 else
-                    xo[set][i - BC] = *reinterpret_cast<const op_t *>(smem + (ad[s][i - BC] ^ (uint32_t)(kk << 5)));
+                    xo[set][i - CB] = *reinterpret_cast<const op_t *>(smem + (ad[s][i - CB] ^ (uint32_t)(kk << 5)));
             };
 
 #pragma unroll
-            for (int b = 0; b < BP; ++b) address1(b, 0, tap_offset(0, 0, 0u));
+            for (int b = 0; b < RB; ++b) address1(b, 0, tap_offset(0, 0, 0u));
             static_for<NOP>([&](auto i) { fetch1(decltype(i)::value, 0, 0, 0, 0); });
             if (rd == 0) make_affine(a.epi, smem_ + K_::RAW0, smem_ + K_::AFF0, TN, tid, K_::NT);
             __builtin_amdgcn_sched_barrier(0);
@@ -282,7 +295,7 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
                         asm volatile("" : "+s"(toff));  // or all nine taps' addresses would be kept in registers
                     }
                     static_for<NM>([&](auto i_) {
-                        constexpr int i = decltype(i_)::value, b = i / BC, c = i % BC;
+                        constexpr int i = decltype(i_)::value, b = i / CB, c = i % CB;
                         acc[b][c] = MF::run(wo[j & 1][c], xo[j & 1][b], acc[b][c]);
                         static_for<NOP>([&](auto q_) {
                             constexpr int q = decltype(q_)::value;
@@ -292,8 +305,8 @@ __global__ __launch_bounds__(kWave * P, 1) void patch_conv_kernel(IgemmArgs a, S
                             }
                         });
                         if constexpr (j % 2 == 0)
-                            static_for<BP>([&](auto b_) {
-                                if constexpr (decltype(b_)::value * NM / BP == i) address1(decltype(b_)::value, (j / 2 + 1) % 3, toff);
+                            static_for<RB>([&](auto b_) {
+                                if constexpr (decltype(b_)::value * NM / RB == i) address1(decltype(b_)::value, (j / 2 + 1) % 3, toff);
                             });
                         if constexpr (j == 5) {
                             if constexpr (i < HEAD) replace(r == 2 ? cc + 2 : cc + 1, cc + 1, r, i);

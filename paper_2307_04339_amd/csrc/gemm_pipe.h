@@ -43,18 +43,36 @@ struct PipeKernel {
     static constexpr int KT = 128 / ES;                   // K per chunk
     static constexpr int NK = 4;                          // k-steps per chunk: 32 bytes of each row
     static constexpr int MPK = ES == 4 ? 4 : 1;           // MFMAs per block and k-step
-    static constexpr int NM = BP * BC * MPK, NOP = BP + BC;
+    // Smaller physical blocks: a wave holds SL logical waves at once and walks K once for all of them (SM
+    // of them along the rows times SN along the columns); the remaining ones in further rounds, each of
+    // which loads the whole tile's operands again.  One at a time 8x56x56x128->256 3x3/2 took 21.7 us in
+    // blocks of 128 and 52.0 of 64; so 13.6 and 20.3 (17.8 and 39.1 by igemm_dma_kernel).  Sixteen blocks
+    // are half of a wave's registers; with them 256x128 tiles spill, up to 165 registers in blocks of 64,
+    // which still beats a second walk there (2048x2304x768 55.1 us against 70.2, in blocks of 128 25.6
+    // against 24.8)
+    static constexpr int MOST = P == 2 ? 8 : 16;           // MFMA blocks
+    static constexpr int FIT = MOST / (BP * BC) >= 4 ? 4 : (MOST / (BP * BC) >= 2 ? 2 : 1);
+    static constexpr int SL = kLogicalWaves / P < FIT ? kLogicalWaves / P : FIT;
+    static constexpr int SN = P == 1 && WN == 2 && SL > 1 ? 2 : 1, SM = SL / SN;
+    static constexpr int MSTEP = SN * P / WN > 0 ? SN * P / WN : 1;  // logical rows between a wave's row slots
+    static constexpr int RB = SM * BP, CB = SN * BC;      // MFMA blocks of a physical wave
+    static constexpr int NM = RB * CB * MPK, NOP = RB + CB;
     static constexpr int LA = NM >= 4 ? 1 : 3;            // k-steps read ahead
     static constexpr int NS = LA + 1;                     // operand sets
     static constexpr int STAGE = (TM + TN) * 128;
     // one workgroup per CU from 128x64 on, two below
     static constexpr int BUDGET = (STAGE >= 24 * 1024 ? 160 : 80) * 1024 - 7 * TN * 4;
-    static constexpr int S_FIT = BUDGET / STAGE, S = S_FIT > 5 ? 5 : S_FIT;
+    static constexpr int S_FIT = BUDGET / STAGE, S_MOST = S_FIT > 5 ? 5 : S_FIT;
+    // with fewer than four waves per workgroup and one step read ahead, three stages if more workgroups then
+    // share a CU (two stages gained no more of them but for 128x128, and there left the loads too little
+    // time: 4096x768x3072 in blocks of 128 46.1 us against 34.0)
+    static constexpr int LDS_CU = 160 * 1024;
+    static constexpr int S = P < 4 && LA == 1 && LDS_CU / (3 * STAGE + 7 * TN * 4) > LDS_CU / (S_MOST * STAGE + 7 * TN * 4) ? 3 : S_MOST;
     static constexpr int NIA = TM / 8 / P, NIB = TN / 8 / P, NL = NIA + NIB;  // loads per wave and chunk
     static constexpr int AHEAD = LA == 1 ? S : S - 1;     // chunks in flight or resident after a refill
     static constexpr int RAW0 = S * STAGE, AFF0 = RAW0 + 5 * TN * 4;
     static constexpr int LDS_BYTES = AFF0 + 2 * TN * 4;
-    static constexpr int ROUNDS = kLogicalWaves / P;
+    static constexpr int ROUNDS = kLogicalWaves / P / SL;
     static constexpr int NST = BP * BC * (ES == 4 ? 4 : 2);
     static constexpr int HEAD = (NL + NK - 1) / NK;       // loads of a refill under the k-step it starts at
     static constexpr int PRE = HEAD + (LA - 1) * (NL - HEAD) / (NK - 1);  // and by the end of its LA-th k-step
@@ -72,7 +90,7 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
     typedef PipeKernel<T, TM, TN, WM, P> K_;
     typedef typename K_::MF MF;
     typedef typename MF::acc_t acc_t;
-    constexpr int WN = K_::WN, BP = K_::BP, BC = K_::BC, NIA = K_::NIA, NIB = K_::NIB, NL = K_::NL, NK = K_::NK, LA = K_::LA;
+    constexpr int WN = K_::WN, BP = K_::BP, BC = K_::BC, RB = K_::RB, CB = K_::CB, SL = K_::SL, NIA = K_::NIA, NIB = K_::NIB, NL = K_::NL, NK = K_::NK, LA = K_::LA;
     constexpr int NS = K_::NS, S = K_::S, NM = K_::NM, NOP = K_::NOP, HEAD = K_::HEAD, PRE = K_::PRE, AHEAD = K_::AHEAD, MPK = K_::MPK;
     constexpr int ROUNDS = K_::ROUNDS, NST = K_::NST, ES = K_::ES, KT = K_::KT, VEC = 16 / ES;
     static_assert(!NB || (ES == 2 && TN == 64 && !TAPS), "[k][n] operands: 16-bit, 64 columns, one tap");
@@ -222,7 +240,7 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
         trace_tile(sh, t, iter);
 #pragma unroll 1
         for (int rd = 0; rd < ROUNDS; ++rd) {
-            acc_t acc[BP][BC];
+            acc_t acc[RB][CB];
             if (!loaded) {
                 decode(td);
                 if ((PIPE ? 0 : iter) + rd > 0) wait_and_meet<0>();  // every wave is done with the ring and the parameters
@@ -235,15 +253,15 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
             loaded = false;
             const uint32_t tm0 = m0, tn0 = n0;
             const int64_t tyoff = yoff;
-            const int lam = rd * P + pw, wm = lam / WN, wn = lam % WN;
+            const int lam = rd * SL * P + pw, wm = lam / WN, wn = lam % WN;  // the round's first slot
 #pragma unroll
-            for (int b = 0; b < BP; ++b)
+            for (int b = 0; b < RB; ++b)
 #pragma unroll
-                for (int c = 0; c < BC; ++c) acc[b][c] = acc_t{};
+                for (int c = 0; c < CB; ++c) acc[b][c] = acc_t{};
 
             // operand addresses: row r of a stage at 128 r, piece 2 kk + hx at slot ^ ((r >> 1) & 7); block
             // offsets are multiples of 32 rows and leave the swizzle alone
-            u32x4 xo[NS][BP], wo[NS][BC];
+            u32x4 xo[NS][RB], wo[NS][CB];
             const uint32_t sw = (uint32_t)(hx ^ ((xl >> 1) & 7)) << 4;
             const uint32_t abase = (uint32_t)(wm * (TM / WM) + xl) * 128u + sw;
             const uint32_t bbase = (uint32_t)(TM + wn * (TN / WN) + xl) * 128u + sw;
@@ -252,10 +270,12 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
             const uint32_t nbase = (uint32_t)(TM * 128) + (uint32_t)(8 * hx + ((lane >> 2) & 3)) * 128u +
                                    ((uint32_t)((((lane >> 3) & 1) << 2) ^ (wn * (TN / WN) / 8) ^ (((lane >> 3) & 2) | ((lane >> 1) & 1))) << 4) +
                                    (uint32_t)(lane & 1) * 8u;
+            // row of the tile, from the wave's first, at which row block b starts
+            auto block_row = [](int b) __attribute__((always_inline)) { return (b / BP) * K_::MSTEP * (TM / WM) + (b % BP) * 32; };
             // operand i (column blocks, then row blocks) of k-step kk of the stage at byte st
             auto fetch1 = [&](int i, int kk, uint32_t st, int set) __attribute__((always_inline)) {
                 if constexpr (NB) {
-                    if (i < BC) {
+                    if (i < CB) {
                         typedef short s16x4 __attribute__((ext_vector_type(4)));
                         typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                         const uint32_t at = lds0 + (nbase ^ (uint32_t)(i << 6)) + st + (uint32_t)(kk * 2048);
@@ -269,8 +289,8 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
                         return;
                     }
                 }
-                if (i < BC) wo[set][i] = *reinterpret_cast<const u32x4 *>(smem + ((bbase ^ (uint32_t)(kk << 5)) + st + i * 4096));
-                else xo[set][i - BC] = *reinterpret_cast<const u32x4 *>(smem + ((abase ^ (uint32_t)(kk << 5)) + st + (i - BC) * 4096));
+                if (i < CB) wo[set][i] = *reinterpret_cast<const u32x4 *>(smem + ((bbase ^ (uint32_t)(kk << 5)) + st + i * 4096));
+                else xo[set][i - CB] = *reinterpret_cast<const u32x4 *>(smem + ((abase ^ (uint32_t)(kk << 5)) + st + block_row(i - CB) * 128));
             };
             static_for<LA>([&](auto k) {
                 static_for<NOP>([&](auto i) { fetch1(decltype(i)::value, decltype(k)::value, 0u, decltype(k)::value); });
@@ -303,7 +323,7 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
                         }
                     }
                     static_for<NM>([&](auto i_) {
-                        constexpr int i = decltype(i_)::value, e = i / (BP * BC), b = i % (BP * BC) / BC, c = i % BC;
+                        constexpr int i = decltype(i_)::value, e = i / (RB * CB), b = i % (RB * CB) / CB, c = i % CB;
                         if constexpr (ES == 4)
                             acc[b][c] = MF::run(__builtin_bit_cast(f32x4, wo[j % NS][c])[e], __builtin_bit_cast(f32x4, xo[j % NS][b])[e], acc[b][c]);
                         else
@@ -342,12 +362,13 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
                 }
             }
             // ---- epilogue
-            trace_wave(sh, t, lam, pw, rd);
+#pragma unroll
+            for (int sl = 0; sl < SL; ++sl) trace_wave(sh, t, lam + sl * P, pw, rd * SL + sl);
             const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(static_cast<T *>(a.y) + tyoff, (short)0, (int)a.y_bytes, 0x00020000);
             const __amdgpu_buffer_rsrc_t rr =
                 __builtin_amdgcn_make_buffer_rsrc(static_cast<T *>(const_cast<void *>(a.res)) + tyoff, (short)0, (int)a.y_bytes, 0x00020000);
             finish_tile<T>(a.epi, smem + K_::AFF0, TN, wn * (TN / WN), tn0, Nc32, ry, rr, acc, [&](int b, int x, uint32_t &row) {
-                const uint32_t m = tm0 + (uint32_t)(wm * (TM / WM) + b * 32 + x);
+                const uint32_t m = tm0 + (uint32_t)(wm * (TM / WM) + block_row(b) + x);
                 row = m * (uint32_t)a.ldy;
                 return m < M32;
             });

@@ -191,10 +191,12 @@ static int pipe_tile_n(int cfg) {
 // igemm_dma_kernel stays, from sweeps of 475 and 144 shapes (its time / this kernel's, us):
 //  - where it takes 32x32 tiles and whole K chunks, one tile per CU at most: 1x76x76x64->160 3x3/2 (230
 //    tiles) 5.4 / 6.5, 500x512x512 (256) 4.8 / 5.5, 1000x256x64 (256) 3.7 / 4.0 (K = 40, decoded per lane,
-//    3.9 / 3.9); or two per CU and more than 12 chunks (8 with several taps): 1000x512x3072 (512 tiles,
-//    48 chunks) 12.8 / 14.9, 10000x24x2048 (313, 32) 10.2 / 12.4, 2000x256x1024 (504, 16) 7.1 / 7.4, but
-//    128x2304x768 (288, 12) 6.5 / 6.5, 2000x256x512 (504, 8) 5.8 / 5.6, 4100x64x192 (258, 3) 4.5 / 4.5,
+//    3.9 / 3.9); or two per CU and more than 8 chunks: 1000x512x3072 (512 tiles, 48 chunks) 12.8 / 14.9,
+//    10000x24x2048 (313, 32) 10.2 / 12.4, 2000x256x1024 (504, 16) 7.1 / 7.4, 128x2304x768 (288, 12) 6.5 / 6.5
+//    and in blocks of 64 8.3 / 9.7; but 2000x256x512 (504, 8) 5.8 / 5.6, 4100x64x192 (258, 3) 4.5 / 4.5,
 //    6x62x62x320->96 3x3/2 (543, 45) 15.4 / 15.1.
+//  - where it takes 128x128 tiles for a single chunk: scores of 96 x 512x512x64 22.4 / 22.2, in blocks of
+//    128 31.6 / 34.7, of 64 58.6 / 68.2.
 //  - where it takes 128x64 tiles and this kernel would take as many, more than one per CU: two of its
 //    workgroups share a CU.  20x50x50x192->64 1x1 (391 tiles) 7.8 / 9.0, 44x50x50x320->24 (860) 16.6 / 21.4,
 //    13x28x111x192->24 5x5 (316) 42.9 / 50.5, 14x100x100x64->24 3x3/2 (274) 10.2 / 12.8; 215 tiles 8.9 / 7.6.
@@ -213,8 +215,9 @@ static int choose_pipe(const miriam_op_desc &d, const IgemmArgs &a, int64_t batc
     if (batch * cdiv(a.M, 64) * cdiv(a.Nc, 64) * (nch <= 12 ? 4 : 2) < cus) return 0;
     if (!nmaj && other == CFG_32 && a.C % kt == 0) {
         const int64_t t32 = batch * cdiv(a.M, 32) * cdiv(a.Nc, 32);
-        if (t32 <= cus || (t32 <= 2 * cus && nch > (taps ? 8 : 12))) return 0;
+        if (t32 <= cus || (t32 <= 2 * cus && nch > 8)) return 0;
     }
+    if (!nmaj && other == CFG_128 && nch == 1) return 0;
     struct Cost { int cfg; int64_t chunk, rest; };
     static const Cost costs[6] = {{CFG_PIPE_64, 220, 1800}, {CFG_PIPE_128x64, 276, 2500}, {CFG_PIPE_128, 420, 3500},
                                   {CFG_PIPE_256x128, 830, 4500}, {CFG_PIPE_256x192, 1350, 6000}, {CFG_PIPE_256x64, 460, 3500}};

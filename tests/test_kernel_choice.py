@@ -52,7 +52,7 @@ def is_pipe(tm, tn, lds):
 
 @pytest.mark.parametrize("m,n,k,pipe", [
     (500, 512, 512, False), (200, 1024, 256, False), (1000, 512, 3072, False), (10000, 24, 2048, False),
-    (2000, 256, 1024, False), (2000, 256, 512, True), (128, 2304, 768, True), (10000, 160, 3072, True),
+    (2000, 256, 1024, False), (2000, 256, 512, True), (128, 2304, 768, False), (128, 2304, 512, True), (10000, 160, 3072, True),
     (50000, 64, 192, False), (40000, 64, 3072, False), (25000, 64, 3072, True), (50000, 64, 144, True),
     (110000, 64, 144, False), (4096, 2304, 768, True),
 ])
@@ -67,3 +67,9 @@ def test_pipeline_needs_rounds_for_products(m, n, k, pipe):
 ])
 def test_pipeline_needs_rounds_for_convolutions(n, h, w, c, k, ks, stride, pipe):
     assert is_pipe(*conv(n, h, w, c, k, ks, stride)) == pipe
+
+
+def test_pipeline_leaves_single_chunk_scores_of_many_tiles():
+    scores = dict(kind=L.OP_BGEMM, dtype=L.BF16, kk=64, batch_div=12, ldx=2304, ldw=2304, sx0=64, sw0=64)
+    assert not is_pipe(*tile_of(m=512, nn=512, batch=96, ldy=512, sy0=512 * 512, **scores))
+    assert is_pipe(*tile_of(m=256, nn=256, batch=48, ldy=256, sy0=256 * 256, **scores))
