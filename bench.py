@@ -117,9 +117,11 @@ def time_layers(net, reps, flush):
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 # device code of the contraction kernels; the host-side choice of kernel is checked through
 # the kernel path and tile recorded with the counters
-KERNEL_SOURCES = ["conv_halo.h", "conv_rw.h", "conv_rw_regs.h", "conv_patch.h", "gemm_pipe.h", "tile_regs.h", "igemm_dma.h",
-                  "igemm.h", "elastic_common.h", "kargs.h", "kern_igemm_f16.hip",
-                  "kern_igemm_bf16.hip", "kern_igemm_f32.hip", "kern_rw.hip", "kern_skinny.hip"]
+KERNEL_SOURCES = ["conv_halo.h", "conv_rw.h", "conv_rw_regs.h", "conv_rw_tile.h", "conv_patch.h", "gemm_pipe.h", "tile_regs.h",
+                  "igemm_dma.h", "igemm.h", "elastic_common.h", "kargs.h", "kern_igemm_f16.hip", "kern_igemm_bf16.hip",
+                  "kern_igemm_f32.hip", "kern_patch_f16.hip", "kern_patch_bf16.hip", "kern_pipe_nb_f16.hip",
+                  "kern_pipe_nb_bf16.hip", "kern_pipe_one_f16.hip", "kern_pipe_one_bf16.hip", "kern_pipe_taps_f16.hip",
+                  "kern_pipe_taps_bf16.hip", "kern_rw.hip", "kern_skinny.hip"]
 
 
 def kernel_source_hash():

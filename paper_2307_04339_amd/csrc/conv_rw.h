@@ -1,65 +1,23 @@
-// Direct convolution with the weights resident in registers, for narrow layers (fp16 /
-// bf16, C <= 64 input channels): here 3x3 stride 1 (at most 64 output channels); 3x3 stride 2
-// (8-channel images) and 1x1 stride 1 (any number of output channels) in conv_rw_regs.h.
+// Direct 3x3 stride-1 convolution with the weights resident in registers, for narrow layers (fp16 / bf16,
+// C in {8, 16, 32, 64}, at most 64 output channels).  3x3 stride 2 on 8-channel images and 1x1 are in
+// conv_rw_regs.h; tile, patch stream, weights, K order and elastic blocks of both in conv_rw_tile.h.
 //
-// The tile is 4 x 32 output pixels of one image times 64 output channels (for 3x3 stride 1
-// the tile of the LDS-patch kernel, so the tile space, the shard plans and the tile map
-// are the same), split 2 x 2 over the 4 logical waves; logical wave (wm, wn) owns tile
-// rows 2wm, 2wm+1 and output channels 32wn .. 32wn+31 of the tile's 64.  Tile id =
-// ((image * tY + tile row) * tX + tile column) * nT + n tile.
-//
-// With at most 64 input channels the whole filter slice of a logical wave, 32
-// channels x KS*KS*C K values, fits its registers as MFMA B operands (9C/4 VGPRs for
-// 3x3: 144 for C = 64), so with one n tile a workgroup loads its weights once and keeps
-// them across every tile it runs; 1x1 layers with several n tiles load the next tile's
-// (C/4 VGPRs) while the current one computes.  Only the input patch of a tile, the
-// ((4-1) ST + KS) x ((32-1) ST + KS) pixels its taps touch, streams through LDS: it is
-// DMA'd (global_load_lds_dwordx4) into one of two buffers while the previous tile
-// computes.  A pixel occupies C/8 16-byte slots, padded to an odd count, so the pixels
-// of a tap map to distinct bank groups and every MFMA operand read is a ds_read_b128 with
-// a compile-time offset.
-//
-// K order per output element (fixed, whatever the elastic configuration): MFMA step s
-// covers k = 16s .. 16s+15 with k = tap * C + c (tap = KS r + s in row-major order, c
-// fastest), the order of the [Cout][KH][KW][Cin] weight rows; when KS*KS*C is not a
-// multiple of 16 the last step's upper half is zero on both operands.
-//
-// Elastic block: a physical block of P waves runs logical wave lambda on wave
-// lambda mod P, as its (lambda div P)-th logical wave.  P = 2 runs both row halves of one
-// channel half (same weights) at once; P = 1 runs the four logical waves in four rounds,
-// loading the weights of each round's channel half.  Each
-// output element sees the same MFMA sequence in every configuration, so results are
-// bit-identical for every shard plan, grid and physical block.
+// There is one n tile, so a workgroup loads its weights once and keeps them across every tile it runs.
+// The finished tile is staged through LDS, over the patch buffer it has been read from where one round
+// suffices, and stored in whole pixel rows.
 #pragma once
 
-#include "igemm_dma.h"
+#include "conv_rw_tile.h"
 
 namespace miriam {
 
-template <class T, int C, int P, int KS, int ST>
-struct RwKernel {
-    typedef Mfma<T, 32> MF;
-    static_assert(sizeof(T) == 2, "16-bit operands only");
-    static_assert(C % 8 == 0 && C >= 8 && C <= 64, "C must be a multiple of 8 up to 64");
-    // two MFMA operand halves share one tap unless one tap holds a single half (C = 8)
-    static_assert(KS == 1 || C == 8 || C % 16 == 0, "3x3 needs C = 8 or a multiple of 16");
-    static_assert((KS == 3 && (ST == 1 || ST == 2)) || (KS == 1 && ST == 1), "3x3 stride 1 or 2, 1x1 stride 1");
-    static constexpr int TH = 4, TW = 32, TM = TH * TW, TN = 64;
-    static constexpr int NT = kWave * P;
-    static constexpr int VEC = 8;                         // 16-bit elements per 16 bytes
-    static constexpr int NP = C / 8;                      // 16-byte pieces of a pixel
-    static constexpr int SP = NP % 2 == 1 ? NP : NP + 1;  // LDS slots per pixel (odd stride)
-    static constexpr int PS = SP * 16;                    // LDS bytes per patch pixel
-    static constexpr int PH = (TH - 1) * ST + KS, PW = (TW - 1) * ST + KS, PPIX = PH * PW;
-    static constexpr int NSLOT = PPIX * SP;
-    static constexpr int NINS = (NSLOT + kWave - 1) / kWave;  // DMA instructions per patch
-    static constexpr int NJ = (NINS + P - 1) / P;             // per wave (the last may be idle)
-    static constexpr int PATCH = NINS * kWave * 16;
-    static constexpr int KTOT = KS * KS * C;
-    static constexpr int NS = (KTOT + 15) / 16;            // MFMA k-steps of 16
-    static constexpr int LW = kLogicalWaves / P;
-    static constexpr int SL = P == 2 ? 2 : 1;              // logical waves held at once
-    static constexpr int ROUNDS = LW / SL;
+template <class T, int C, int P>
+struct RwKernel : RwTile<T, C, P, 3, 1> {
+    typedef RwTile<T, C, P, 3, 1> Tile;
+    using Tile::TM;
+    using Tile::TN;
+    using Tile::PATCH;
+    using Tile::ROUNDS;
     static constexpr int LDC = TN + 4;                     // staged fp32 row (residual epilogue)
     static constexpr int LDY = TN + 8;                     // staged output row in elements
     static constexpr int CS = TM * LDC * 4;
@@ -68,27 +26,17 @@ struct RwKernel {
     static constexpr int BUF = OVERLAY ? (PATCH > CS ? PATCH : CS) : PATCH;
     static constexpr int LDS_BYTES = 2 * BUF + (OVERLAY ? 0 : CS);
     static constexpr int WAVES_PER_SIMD = (P == 4 && 2 * (LDS_BYTES + 16) <= 160 * 1024) ? 2 : 1;
-    static_assert(LW % SL == 0, "slots");
     static_assert(TM * LDY * 2 <= CS, "staged output fits the staging area");
 };
 
-// patch pixel offset of filter tap `tap` (row-major KS x KS)
-template <int PW, int KS>
-__host__ __device__ constexpr int rw_toff(int tap) {
-    return (tap / KS) * PW + tap % KS;
-}
-
-template <class T, int C, int P, int KS, int ST>
-__global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P, KS, ST>::WAVES_PER_SIMD)) void rw_conv_kernel(IgemmArgs a,
-                                                                                                     Shard sh) {
-    typedef RwKernel<T, C, P, KS, ST> K_;
+template <class T, int C, int P>
+__global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P>::WAVES_PER_SIMD)) void rw_conv_kernel(IgemmArgs a, Shard sh) {
+    typedef RwKernel<T, C, P> K_;
     typedef typename K_::MF MF;
-    typedef typename MF::op_t op_t;
-    typedef typename MF::acc_t acc_t;
-    constexpr int TW = K_::TW, TM = K_::TM, TN = K_::TN, PW = K_::PW, PS = K_::PS, SP = K_::SP, NP = K_::NP;
-    constexpr int NT = K_::NT, VEC = K_::VEC, NS = K_::NS, SL = K_::SL, ROUNDS = K_::ROUNDS;
-    constexpr int LDC = K_::LDC, LDY = K_::LDY;
-    constexpr int KTOT = K_::KTOT, NJ = K_::NJ, NINS = K_::NINS, BUF = K_::BUF;
+    typedef typename K_::op_t op_t;
+    typedef typename K_::acc_t acc_t;
+    constexpr int TW = K_::TW, TM = K_::TM, TN = K_::TN, NT = K_::NT, VEC = K_::VEC, NS = K_::NS, SL = K_::SL, ROUNDS = K_::ROUNDS;
+    constexpr int LDC = K_::LDC, LDY = K_::LDY, BUF = K_::BUF;
 
     __shared__ __attribute__((aligned(1024))) char smem_[K_::LDS_BYTES];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem_;
@@ -97,60 +45,20 @@ __global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P, KS, ST>::WAVES_PER_SI
     const int pw = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = tid % kWave;
     const int hx = lane >> 5, xl = lane & 31;  // MFMA operand half, pixel column / channel
-    const T *__restrict__ X = static_cast<const T *>(a.x);
-    const T *__restrict__ Wt = static_cast<const T *>(a.w);
     T *__restrict__ Y = static_cast<T *>(a.y);
     const T *__restrict__ R = static_cast<const T *>(a.res);
     const int64_t G = gridDim.x;
     const int64_t rank = wg_rank(blockIdx.x, G);
     const int64_t end = sh.begin + sh.len;
-    const int32_t H32 = (int32_t)a.H, W32 = (int32_t)a.W, Ho32 = (int32_t)a.Ho, Wo32 = (int32_t)a.Wo;
-    const int32_t ldx32 = (int32_t)a.ldx;
-    const uint32_t tX32 = (uint32_t)a.tX, tY32 = (uint32_t)a.tY, nT32 = (uint32_t)a.nT;
+    const int32_t Ho32 = (int32_t)a.Ho, Wo32 = (int32_t)a.Wo;
     const bool has_res = (a.epi.flags & EPI_RES) != 0;
 
     int64_t t = sh.begin + rank;
     if (t >= end) return;
 
-    // weights of n tile nt, channel half wn: step s holds k = 16s + 8hx .. +7 of output
-    // channel 64 nt + 32 wn + xl
-    op_t bw[NS];
-    auto load_weights = [&](op_t *dst, uint32_t nt, int wn) {
-        const int64_t n = 64 * (int64_t)nt + 32 * wn + xl;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int k = 16 * s + 8 * hx;
-            op_t v = op_t{};
-            if (n < a.Nc && k < KTOT) v = *reinterpret_cast<const op_t *>(Wt + n * a.ldw + k);
-            dst[s] = v;
-        }
-    };
     // P = 4: logical wave pw; P = 2: channel half pw, both row halves; P = 1: both, in rounds
     const int wn_mine = P == 4 ? (pw & 1) : (P == 2 ? pw : 0);
 
-    // tile id = ((image * tY + tile row) * tX + tile column) * nT + n tile, kept as mixed-radix
-    // digits that advance by the grid (no division per tile)
-    struct Cursor {
-        uint32_t img, ty, tx, nt;
-    };
-    const uint32_t g0 = (uint32_t)G;
-    const uint32_t gn = g0 % nT32, g1 = g0 / nT32;
-    const uint32_t gx = g1 % tX32, g2 = g1 / tX32;
-    const uint32_t gy = g2 % tY32, gi = g2 / tY32;
-    auto advance = [&](Cursor c) {
-        c.nt += gn;
-        const uint32_t cn = c.nt >= nT32 ? 1u : 0u;
-        c.nt -= cn * nT32;
-        c.tx += gx + cn;
-        const uint32_t cx = c.tx >= tX32 ? 1u : 0u;
-        c.tx -= cx * tX32;
-        c.ty += gy + cx;
-        const uint32_t cy = c.ty >= tY32 ? 1u : 0u;
-        c.ty -= cy * tY32;
-        c.img += gi + cy;
-        return c;
-    };
-    const bool one_nt = nT32 == 1;
     // per-channel affine part of the epilogue folded into one multiply-add, v = acc * sc + sh,
     // for this lane's channel in each round (bias, then batch norm)
     float esc[ROUNDS], esh[ROUNDS];
@@ -163,55 +71,14 @@ __global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P, KS, ST>::WAVES_PER_SI
         }
     };
 
-    // DMA of the patch of tile `c` into buffer `buf`: instruction j writes slots 64j .. 64j+63.
-    // The slot a lane fills is the same in every tile, so its decode (patch row and column,
-    // 16-byte piece, whether the slot holds data) is done once and kept packed in one register
-    // per instruction: bits [0, 7) column, [7, 11) row, [11, 15) piece, bit 15 set for a data
-    // slot.  Per tile a lane then only adds the tile's origin, checks the image bounds and
-    // forms a 32-bit byte offset into the image (the library admits the kernel only for images
-    // of less than 2^31 bytes); pixels outside the image and padding slots take an offset past
-    // the buffer, which reads zeros.
-    static_assert(K_::PW < 128 && K_::PH <= 16 && SP <= 16, "packed patch geometry");
-    uint32_t geo[NJ];
-#pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) {
-        const int j = jj * P + pw;
-        const int q = j * kWave + lane;
-        const int pr = q / SP, sl = q - (q / SP) * SP;
-        const int prow = pr / PW, pcol = pr - (pr / PW) * PW;
-        const bool ok = j < NINS && pr < K_::PPIX && sl < NP;
-        geo[jj] = ok ? ((uint32_t)pcol | ((uint32_t)prow << 7) | ((uint32_t)sl << 11) | (1u << 15)) : 0u;
-    }
-    const uint32_t img_bytes = (uint32_t)(a.img_x * (int64_t)sizeof(T));
-    auto issue_patch = [&](Cursor c, int buf) {
-        const uint32_t tx = c.tx, ty = c.ty, img = c.img;
-        const int32_t iy0 = (int32_t)ty * K_::TH * ST - a.pad, ix0 = (int32_t)tx * TW * ST - a.pad;
-        const rsrc_t rs = make_rsrc(X + (int64_t)img * a.img_x, img_bytes);
-        const uint32_t base = lds0 + (uint32_t)(buf * BUF);
-#pragma unroll
-        for (int jj = 0; jj < NJ; ++jj) {
-            const int j = jj * P + pw;
-            if (j < NINS) {
-                const uint32_t g = geo[jj];
-                const int32_t iy = iy0 + (int32_t)((g >> 7) & 15u), ix = ix0 + (int32_t)(g & 127u);
-                const bool ok = (g >> 15) != 0u && (uint32_t)iy < (uint32_t)H32 && (uint32_t)ix < (uint32_t)W32;
-                const uint32_t off = (uint32_t)((iy * W32 + ix) * ldx32 + (int32_t)((g >> 11) & 15u) * VEC) * (uint32_t)sizeof(T);
-                buf_dma16(ok ? off : kOutOfRange, rs, 0u, base + (uint32_t)(j * kWave * 16));
-            }
-        }
-    };
-
-    Cursor cu;
-    {
-        const uint32_t t32 = (uint32_t)t, r1 = t32 / nT32, r2 = r1 / tX32;
-        cu = Cursor{r2 / tY32, r2 % tY32, r1 % tX32, t32 % nT32};
-    }
-    // one n tile: weights and per-channel constants once for the workgroup's lifetime;
-    // several (1x1 only): for each tile, the next tile's weights load with its patch
-    op_t bw_next[KS == 1 ? NS : 1];
-    if constexpr (P != 1) load_weights(bw, cu.nt, wn_mine);
+    const RwWalk walk(a, (uint32_t)G);
+    const RwPatch<K_> stream(pw, lane);
+    RwCursor cu = walk.at((uint32_t)t);
+    // weights and per-channel constants once for the workgroup's lifetime
+    op_t bw[NS];
+    if constexpr (P != 1) rw_load_weights<K_>(a, bw, cu.nt, wn_mine, lane);
     load_affine(cu.nt);
-    issue_patch(cu, 0);
+    stream.issue(a, cu, lds0, pw);
     int iter = 0;
     for (; t < end; t += G, ++iter) {
         trace_tile(sh, t, iter);
@@ -220,24 +87,10 @@ __global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P, KS, ST>::WAVES_PER_SI
         // is done with the other buffer (the previous tile's staged outputs)
         wait_vmcnt<0>();
         __syncthreads();
-        const Cursor nx = advance(cu);
-        if constexpr (KS == 1 && P != 1) {
-            if (!one_nt && iter > 0) {
-                // the weights loaded with this tile's patch (complete: waited above)
-#pragma unroll
-                for (int s = 0; s < NS; ++s) bw[s] = bw_next[s];
-                load_affine(cu.nt);
-            }
-        }
-        if (t + G < end) {
-            issue_patch(nx, cur ^ 1);
-            if constexpr (KS == 1 && P != 1)
-                if (!one_nt) load_weights(bw_next, nx.nt, wn_mine);
-        }
+        const RwCursor nx = walk.advance(cu);
+        if (t + G < end) stream.issue(a, nx, lds0 + (uint32_t)((cur ^ 1) * BUF), pw);
 
         const uint32_t tx = cu.tx, ty = cu.ty, img = cu.img, ntile = cu.nt;
-        if constexpr (P == 1)
-            if (!one_nt && iter > 0) load_affine(ntile);
         cu = nx;
         const int32_t oy0 = (int32_t)ty * K_::TH, ox0 = (int32_t)tx * TW;
         const char *patch = smem_ + cur * BUF;
@@ -251,54 +104,15 @@ __global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P, KS, ST>::WAVES_PER_SI
             // logical wave lambda = (rd SL + sl) P + pw owns tile rows 2 wm, 2 wm + 1 and channel
             // half wn, with wm = lambda div 2 and wn = lambda mod 2
             const int wn = P == 1 ? (rd & 1) : wn_mine;
-            if constexpr (P == 1) load_weights(bw, ntile, wn);
-            // operand base of block i of slot sl: patch pixel (tile row y, column xl) + this lane's half
-            const char *abase[SL][2];
-#pragma unroll
-            for (int sl = 0; sl < SL; ++sl) {
-                const int wm = P == 4 ? (pw >> 1) : (P == 2 ? sl : (rd >> 1));
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int y = 2 * wm + i;
-                    abase[sl][i] = patch + (y * ST * PW + xl * ST) * PS + (NP == 1 ? 0 : hx * 16);
-                }
-            }
-            // operands of k-step s for every block; one 8-channel tap per operand half (C = 8,
-            // 3x3): halves take taps 2s and 2s+1
-            auto fetch = [&](int s, op_t (&av)[SL][2]) {
-#pragma unroll
-                for (int sl = 0; sl < SL; ++sl)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        if constexpr (NP == 1 && KS == 3) {
-                            const int t0 = 2 * s, t1 = 2 * s + 1;
-                            const int off0 = rw_toff<PW, KS>(t0) * PS;
-                            const int d1 = t1 < 9 ? (rw_toff<PW, KS>(t1) - rw_toff<PW, KS>(t0)) * PS : PS;
-                            op_t v = *reinterpret_cast<const op_t *>(abase[sl][i] + off0 + hx * d1);
-                            if (16 * s + 8 * hx >= KTOT) v = op_t{};
-                            av[sl][i] = v;
-                        } else {
-                            // both halves in one tap (channels c0 .. c0 + 15); 1x1: the one tap
-                            const int k0 = 16 * s, tap = KS == 1 ? 0 : k0 / C, c0 = KS == 1 ? k0 : k0 % C;
-                            const int off = rw_toff<PW, KS>(tap) * PS + (c0 / 8) * 16;
-                            op_t v = *reinterpret_cast<const op_t *>(abase[sl][i] + off);
-                            if (KTOT % 16 != 0 && 16 * s + 8 * hx >= KTOT) v = op_t{};
-                            av[sl][i] = v;
-                        }
-                    }
-            };
-            // Software pipeline in program order: the operand reads of step s + LA are issued
-            // before the MFMAs of step s, and a scheduling fence after each step keeps the
-            // compiler from sinking the reads next to their use (it otherwise waited on every
-            // read and ran each block's MFMAs as one dependent chain).  Within a step the
-            // blocks' MFMAs are independent.
-            constexpr int LA = SL == 1 ? 2 : 1;
+            if constexpr (P == 1) rw_load_weights<K_>(a, bw, ntile, wn, lane);
+            const RwOperands<K_> pixels(patch, pw, rd, hx, xl);
+            constexpr int LA = kRwAhead<K_>;
             op_t opnd[LA + 1][SL][2];
 #pragma unroll
-            for (int s = 0; s < LA && s < NS; ++s) fetch(s, opnd[s]);
+            for (int s = 0; s < LA && s < NS; ++s) pixels.fetch(s, opnd[s]);
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                if (s + LA < NS) fetch(s + LA, opnd[(s + LA) % (LA + 1)]);
+                if (s + LA < NS) pixels.fetch(s + LA, opnd[(s + LA) % (LA + 1)]);
 #pragma unroll
                 for (int sl = 0; sl < SL; ++sl)
 #pragma unroll
@@ -313,12 +127,12 @@ __global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P, KS, ST>::WAVES_PER_SI
             const int col = 32 * wn + xl;
 #pragma unroll
             for (int sl = 0; sl < SL; ++sl)
-                trace_wave(sh, t, 2 * (P == 4 ? (pw >> 1) : (P == 2 ? sl : (rd >> 1))) + wn, pw, rd * SL + sl);
+                trace_wave(sh, t, 2 * K_::row_half(pw, rd, sl) + wn, pw, rd * SL + sl);
             auto stage1 = [&](auto actc) {
                 constexpr int ACT = decltype(actc)::value;
 #pragma unroll
                 for (int sl = 0; sl < SL; ++sl) {
-                    const int wm = P == 4 ? (pw >> 1) : (P == 2 ? sl : (rd >> 1));
+                    const int wm = K_::row_half(pw, rd, sl);
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
                         // element e of the block sits at tile column x = 8 (e / 4) + 4 hx + e % 4
@@ -415,22 +229,23 @@ __global__ __launch_bounds__(kWave * P, (RwKernel<T, C, P, KS, ST>::WAVES_PER_SI
     }
 }
 
-template <class T, int C, int KS, int ST>
-inline void rw_table(const void *out[3], int *lds) {
-    out[0] = reinterpret_cast<const void *>(&rw_conv_kernel<T, C, 1, KS, ST>);
-    out[1] = reinterpret_cast<const void *>(&rw_conv_kernel<T, C, 2, KS, ST>);
-    out[2] = reinterpret_cast<const void *>(&rw_conv_kernel<T, C, 4, KS, ST>);
-    *lds = RwKernel<T, C, 4, KS, ST>::LDS_BYTES;
+template <class T, int C>
+inline int rw_table(const void *out[3], int *lds) {
+    out[0] = reinterpret_cast<const void *>(&rw_conv_kernel<T, C, 1>);
+    out[1] = reinterpret_cast<const void *>(&rw_conv_kernel<T, C, 2>);
+    out[2] = reinterpret_cast<const void *>(&rw_conv_kernel<T, C, 4>);
+    *lds = RwKernel<T, C, 4>::LDS_BYTES;
+    return 0;
 }
 
 // Kernel table for 3x3 stride 1 with C in {8, 16, 32, 64}; -1 otherwise.
 template <class T>
 inline int rw_table_c(int64_t c, const void *out[3], int *lds) {
     switch (c) {
-    case 8: rw_table<T, 8, 3, 1>(out, lds); return 0;
-    case 16: rw_table<T, 16, 3, 1>(out, lds); return 0;
-    case 32: rw_table<T, 32, 3, 1>(out, lds); return 0;
-    case 64: rw_table<T, 64, 3, 1>(out, lds); return 0;
+    case 8: return rw_table<T, 8>(out, lds);
+    case 16: return rw_table<T, 16>(out, lds);
+    case 32: return rw_table<T, 32>(out, lds);
+    case 64: return rw_table<T, 64>(out, lds);
     default: return -1;
     }
 }

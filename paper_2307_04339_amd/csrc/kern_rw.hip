@@ -1,4 +1,5 @@
 // Kernel tables of the resident-weight direct convolution (fp16 and bf16).
+#include "conv_rw.h"
 #include "conv_rw_regs.h"
 
 namespace miriam {
