@@ -164,9 +164,10 @@ def roofline_of(k, dtype):
 
 
 def index_function_cost(net, reps, flush, lib_mod):
-    """Unsharded time of every layer on the pipelined contraction kernel with the
-    computation-based index function (the default) and with the memory-based one (row
-    indices from a host-computed table staged in LDS), median over `reps` cold launches."""
+    """Unsharded time of every contraction on the four-stage pipelined kernel, at the tile it
+    takes there, with the computation-based index function (the default) and with the
+    memory-based one (row indices from a host-computed table staged in LDS), median over `reps`
+    cold launches.  Layers that split K there are left out."""
     import torch
 
     def med(op):
@@ -185,17 +186,22 @@ def index_function_cost(net, reps, flush, lib_mod):
         return 1000.0 * float(np.median(ts))
 
     rows = []
+    tiles = {(32, 32): 1, (64, 64): 2, (128, 128): 3, (128, 64): 4}  # descriptor codes
     for layer in net.layers:
         op = layer.op
         if op.info.path not in (lib_mod.PATH_DMA, lib_mod.PATH_DMA_UNIFORM) or op.info.ksplit > 1:
             continue
         twin = op.variant(flags=op.desc.flags | lib_mod.INDEX_MEMORY)
+        computed = None
         try:
-            if (twin.info.tile_m, twin.info.tile_n) != (op.info.tile_m, op.info.tile_n):
+            if twin.info.ksplit > 1:
                 continue
-            c_us, m_us = med(op), med(twin)
+            computed = op.variant(tile=tiles[(twin.info.tile_m, twin.info.tile_n)], ksplit=1)
+            c_us, m_us = med(computed), med(twin)
         finally:
             twin.destroy()
+            if computed is not None:
+                computed.destroy()
         rows.append(dict(name=layer.name, compute_us=round(c_us, 2), memory_us=round(m_us, 2),
                          memory_over_compute=round(m_us / c_us, 4)))
     return rows

@@ -75,9 +75,11 @@ enum {
      * host computes, at creation, every output row's (image, first input row, first input
      * column) into a device table owned by the op, and each tile stages its rows of the table in
      * LDS instead of dividing the row index in the kernel (memory-based index function; the
-     * default is computation-based).  Results are bitwise the same.  Served by the pipelined
-     * contraction kernel only: the op is created on it (16-byte aligned K-major operands; an
-     * explicit tile must be 1..4), else creation fails with MIRIAM_EINVAL. */
+     * default is computation-based).  Served by the four-stage pipelined contraction kernel only:
+     * the op is created on it (16-byte aligned K-major operands; an explicit tile must be 1..4),
+     * else creation fails with MIRIAM_EINVAL.  Results are bitwise those of the op without the
+     * flag created with the same explicit tile and ksplit (where the library chooses, another
+     * kernel may serve that op, with sums in another order). */
     MIRIAM_INDEX_MEMORY = 8
 };
 
@@ -148,10 +150,10 @@ typedef struct miriam_op_info {
     int32_t full_grid;        /* grid of the op's whole-tile-space (unsharded) launch: num_tiles (one
                                  workgroup per tile); for kernels that keep operands resident
                                  across tiles the workgroups that fit the device at once; for the
-                                 global->LDS pipelined contraction (paths 2 and 3) with one to two
-                                 rounds of resident workgroups' worth of tiles, half the tiles (two
-                                 per workgroup); for its 256-pixel 3x3 variant the fewest workgroups
-                                 that keep the number of rounds */
+                                 four-stage pipelined contraction with one to two rounds of
+                                 resident workgroups' worth of tiles, half the tiles (two per
+                                 workgroup); for the register-tile pipeline and the 3x3 patch kernel
+                                 the fewest workgroups that keep the number of rounds */
 } miriam_op_info;
 
 /* Kernel family behind an op (diagnostic; results do not depend on it beyond rounding
@@ -159,11 +161,13 @@ typedef struct miriam_op_info {
 typedef enum miriam_kernel_path {
     MIRIAM_PATH_OTHER = 0,       /* memory-bound operator kernels */
     MIRIAM_PATH_STAGED = 1,      /* contraction, operands staged through registers */
-    MIRIAM_PATH_DMA = 2,         /* contraction, global->LDS pipeline, per-lane K decode (or mask of the
-                                    last K chunk) */
-    MIRIAM_PATH_DMA_UNIFORM = 3, /* contraction, global->LDS pipeline, chunk-uniform filter taps; with
-                                    tile_m 256, the variant that keeps a 3x3 stride-1 tile's input
-                                    pixels in LDS for all nine taps */
+    MIRIAM_PATH_DMA = 2,         /* contraction, global->LDS pipeline, K that is no whole 128-byte chunks
+                                    per filter tap (decoded per lane, or the last chunk masked) */
+    MIRIAM_PATH_DMA_UNIFORM = 3, /* contraction, global->LDS pipeline, whole chunks per filter tap.
+                                    Three kernels report 2 and 3 and differ in lds_bytes: the
+                                    four-stage pipeline (any tile), the register-tile pipeline (any
+                                    tile of 64 rows or more) and, for 3x3 stride 1, the patch kernel
+                                    that keeps the tile's 256 input pixels in LDS for all nine taps */
     MIRIAM_PATH_SKINNY = 4,      /* small-batch fully connected, K split over logical waves */
     MIRIAM_PATH_HALO = 5,        /* direct 3x3 stride-1 convolution, input patch of the tile in LDS */
     MIRIAM_PATH_RESIDENT = 6     /* direct 3x3 stride-1 convolution, weights resident in registers

@@ -1,6 +1,7 @@
 // Pipelined contraction that keeps a whole tile in the registers of one wave per SIMD: products,
 // strided batched products and convolutions whose K chunks lie inside one filter tap (any K for one
-// tap, C a multiple of the chunk otherwise), 16-byte rows, K-major operands.
+// tap, C a multiple of the chunk otherwise), fp16 / bf16, 16-byte rows, K-major operands (or, for one tap,
+// the right one stored [k][n]).
 //
 // What bounded the 4-stage kernel it replaces for these (igemm_dma_kernel) was the serial chain per
 // 128-byte K chunk: meet, issue the loads, read the operands from LDS, multiply.  Two workgroups per
@@ -9,16 +10,15 @@
 // loads that refill the ring, one at a time; the workgroup meets once per chunk.  The next tile's
 // first loads are issued under the current tile's epilogue, which stores from registers.
 //
-// LDS: a ring of S stages of one 128-byte K chunk (64 16-bit or 32 fp32 values) of the TM output
-// rows' and the TN output columns' operand rows, XOR-swizzled as in igemm_dma.h.  LA is how many
-// k-steps ahead operands are read: one where a k-step holds four or more MFMAs, three for the small
-// tiles, whose k-steps are shorter than the LDS latency.  With LA = 1 the wait before the last k-step
-// also covers the chunk's own LDS reads, so its stage is refilled at once; with LA = 3 the stage of
-// the chunk before is.
+// LDS: a ring of S stages of one 128-byte K chunk (64 values) of the TM output rows' and the TN output
+// columns' operand rows, XOR-swizzled as in igemm_dma.h.  LA is how many k-steps ahead operands are read:
+// one where a k-step holds four or more MFMAs, three for the small tiles, whose k-steps are shorter than
+// the LDS latency.  With LA = 1 the wait before the last k-step also covers the chunk's own LDS reads, so
+// its stage is refilled at once; with LA = 3, where LDS operations stay outstanding over the meeting, the
+// stage of the chunk before is, and the writer of the epilogue's parameters waits for its writes itself.
 //
 // MFMA rows are output columns (channels) and MFMA columns output rows, as in the patch kernel, so
-// that the epilogue stores 16 bytes per lane without staging.  fp32: a lane's 16-byte operand piece
-// holds four K values, one per MFMA.
+// that the epilogue stores 16 bytes per lane without staging.
 //
 // What bounds it: the load path.  128x128 chunks of a K = 3072 product arrive at 34 bytes per clock and
 // CU, 0.42 us a chunk on 0.21 us of MFMA; wider tiles need fewer bytes per flop but leave CUs idle on
@@ -39,10 +39,9 @@ struct PipeKernel {
     static constexpr int WN = kLogicalWaves / WM;
     static constexpr int BP = TM / WM / 32, BC = TN / WN / 32;
     static constexpr int NT = kWave * P;
-    static constexpr int ES = (int)sizeof(T);
-    static constexpr int KT = 128 / ES;                   // K per chunk
+    static_assert(sizeof(T) == 2, "16-bit operands only");
+    static constexpr int KT = 64;                         // K per chunk
     static constexpr int NK = 4;                          // k-steps per chunk: 32 bytes of each row
-    static constexpr int MPK = ES == 4 ? 4 : 1;           // MFMAs per block and k-step
     // Smaller physical blocks: a wave holds SL logical waves at once and walks K once for all of them (SM
     // of them along the rows times SN along the columns); the remaining ones in further rounds, each of
     // which loads the whole tile's operands again.  One at a time 8x56x56x128->256 3x3/2 took 21.7 us in
@@ -56,7 +55,7 @@ struct PipeKernel {
     static constexpr int SN = P == 1 && WN == 2 && SL > 1 ? 2 : 1, SM = SL / SN;
     static constexpr int MSTEP = SN * P / WN > 0 ? SN * P / WN : 1;  // logical rows between a wave's row slots
     static constexpr int RB = SM * BP, CB = SN * BC;      // MFMA blocks of a physical wave
-    static constexpr int NM = RB * CB * MPK, NOP = RB + CB;
+    static constexpr int NM = RB * CB, NOP = RB + CB;        // MFMAs and operand reads per k-step
     static constexpr int LA = NM >= 4 ? 1 : 3;            // k-steps read ahead
     static constexpr int NS = LA + 1;                     // operand sets
     static constexpr int STAGE = (TM + TN) * 128;
@@ -73,7 +72,7 @@ struct PipeKernel {
     static constexpr int RAW0 = S * STAGE, AFF0 = RAW0 + 5 * TN * 4;
     static constexpr int LDS_BYTES = AFF0 + 2 * TN * 4;
     static constexpr int ROUNDS = kLogicalWaves / P / SL;
-    static constexpr int NST = BP * BC * (ES == 4 ? 4 : 2);
+    static constexpr int NST = BP * BC * 2;
     static constexpr int HEAD = (NL + NK - 1) / NK;       // loads of a refill under the k-step it starts at
     static constexpr int PRE = HEAD + (LA - 1) * (NL - HEAD) / (NK - 1);  // and by the end of its LA-th k-step
     static_assert(S >= (LA == 1 ? 2 : 3), "ring");
@@ -91,9 +90,9 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
     typedef typename K_::MF MF;
     typedef typename MF::acc_t acc_t;
     constexpr int WN = K_::WN, BP = K_::BP, BC = K_::BC, RB = K_::RB, CB = K_::CB, SL = K_::SL, NIA = K_::NIA, NIB = K_::NIB, NL = K_::NL, NK = K_::NK, LA = K_::LA;
-    constexpr int NS = K_::NS, S = K_::S, NM = K_::NM, NOP = K_::NOP, HEAD = K_::HEAD, PRE = K_::PRE, AHEAD = K_::AHEAD, MPK = K_::MPK;
-    constexpr int ROUNDS = K_::ROUNDS, NST = K_::NST, ES = K_::ES, KT = K_::KT, VEC = 16 / ES;
-    static_assert(!NB || (ES == 2 && TN == 64 && !TAPS), "[k][n] operands: 16-bit, 64 columns, one tap");
+    constexpr int NS = K_::NS, S = K_::S, NM = K_::NM, NOP = K_::NOP, HEAD = K_::HEAD, PRE = K_::PRE, AHEAD = K_::AHEAD;
+    constexpr int ROUNDS = K_::ROUNDS, NST = K_::NST, ES = 2, KT = K_::KT, VEC = 8;
+    static_assert(!NB || (TN == 64 && !TAPS), "[k][n] operands: 64 columns, one tap");
     constexpr bool PIPE = P == 4 && LA == 1;  // next tile's first loads under the current epilogue
 
     __shared__ __attribute__((aligned(1024))) char smem_[K_::LDS_BYTES];
@@ -323,12 +322,9 @@ __global__ __launch_bounds__(kWave * P, (P == 4 && PipeKernel<T, TM, TN, WM, P>:
                         }
                     }
                     static_for<NM>([&](auto i_) {
-                        constexpr int i = decltype(i_)::value, e = i / (RB * CB), b = i % (RB * CB) / CB, c = i % CB;
-                        if constexpr (ES == 4)
-                            acc[b][c] = MF::run(__builtin_bit_cast(f32x4, wo[j % NS][c])[e], __builtin_bit_cast(f32x4, xo[j % NS][b])[e], acc[b][c]);
-                        else
-                            acc[b][c] = MF::run(__builtin_bit_cast(typename MF::op_t, wo[j % NS][c]),
-                                                __builtin_bit_cast(typename MF::op_t, xo[j % NS][b]), acc[b][c]);
+                        constexpr int i = decltype(i_)::value, b = i / CB, c = i % CB;
+                        acc[b][c] = MF::run(__builtin_bit_cast(typename MF::op_t, wo[j % NS][c]),
+                                            __builtin_bit_cast(typename MF::op_t, xo[j % NS][b]), acc[b][c]);
                         // this MFMA's share of the operand reads LA k-steps ahead
                         static_for<NOP>([&](auto q_) {
                             constexpr int q = decltype(q_)::value;

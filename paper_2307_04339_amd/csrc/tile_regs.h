@@ -100,7 +100,7 @@ __device__ __forceinline__ void exchange16(u32x4 &a, u32x4 &b) {
 // Epilogue of a wave's BP x BC blocks from registers: v = acc * sc + sh (+ residual), activation, one
 // rounding, 16-byte stores.  Accumulator rows are output channels and columns output rows m: lane
 // (hx, xl) of block (b, c) holds channels 8 q + 4 hx .. + 3 of quarter q for row xl of the block;
-// row_of(b, x, row) places row x (in elements; false if outside).  16-bit types: a v_permlane32_swap
+// row_of(b, x, row) places row x (in elements; false if outside).  A v_permlane32_swap
 // per packed pair gives lanes 0..31 channels 16 h .. + 7 and lanes 32..63 16 h + 8 .. + 15, whole
 // 16-byte pieces, and a v_permlane16_swap of the h = 0 and h = 1 pieces puts the four pieces of a
 // row into one store: 64 contiguous bytes per row (32 without it: 96 x 512 x 512 x 64 products, all
@@ -111,6 +111,7 @@ __device__ __forceinline__ void exchange16(u32x4 &a, u32x4 &b) {
 template <class T, bool KEEP = true, class Acc, int BP, int BC, class Rows>
 __device__ __forceinline__ void finish_tile(const Epilogue &e, const char *aff0, int TN, int nl0, uint32_t n0, uint32_t Nc,
                                             __amdgpu_buffer_rsrc_t ry, __amdgpu_buffer_rsrc_t rr, Acc (&acc)[BP][BC], Rows &&row_of) {
+    static_assert(sizeof(T) == 2, "16-bit results only");
     const int lane = threadIdx.x % kWave, hx = lane >> 5;
     auto finish = [&](auto actc, auto resc) {
         constexpr int ACT = decltype(actc)::value;
@@ -130,81 +131,61 @@ __device__ __forceinline__ void finish_tile(const Epilogue &e, const char *aff0,
             }
 #pragma unroll
             for (int b = 0; b < BP; ++b) {
-                if constexpr (sizeof(T) == 4) {
+                // stored piece of this lane: channels 8 pc .. + 7 of rows (lane & 15) and 16 + (lane & 15)
+                const int pc = ((lane >> 5) & 1) | ((lane >> 3) & 2);
+                const uint32_t n = n0 + (uint32_t)(nl + 8 * pc);
+                uint32_t off[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
                     uint32_t row;
-                    const bool in = row_of(b, lane & 31, row);
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        if constexpr (!KEEP) affine(g);
-                        const uint32_t n = n0 + (uint32_t)(nl + 8 * g + 4 * hx);
-                        const uint32_t off = in & (n < Nc) ? (row + n) * 4u : kOutOfRange;
-                        f32x4 r = {0.0f, 0.0f, 0.0f, 0.0f}, o;
-                        if constexpr (RES) r = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off, 0, 0));
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            float v = acc[b][c][4 * g + u] * sc[g][u] + shf[g][u];
-                            if constexpr (RES) v += r[u];
-                            o[u] = act_t<T, ACT>(v);
-                        }
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), ry, (int)off, 0, 0);
-                    }
-                } else {
-                    // stored piece of this lane: channels 8 pc .. + 7 of rows (lane & 15) and 16 + (lane & 15)
-                    const int pc = ((lane >> 5) & 1) | ((lane >> 3) & 2);
-                    const uint32_t n = n0 + (uint32_t)(nl + 8 * pc);
-                    uint32_t off[2];
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        uint32_t row;
-                        const bool in = row_of(b, 16 * h + (lane & 15), row);
-                        off[h] = in & (n < Nc) ? (row + n) * 2u : kOutOfRange;
-                    }
-                    u32x4 o[2], r[2];
-                    if constexpr (RES) {
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) r[h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off[h], 0, 0));
-                        exchange16(r[0], r[1]);
-                    }
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {  // channels 16 h .. 16 h + 15 of the block, quarters 2 h and 2 h + 1
-                        uint32_t q[2][2], rq[2][2];
-#pragma unroll
-                        for (int k = 0; k < 2; ++k) {
-                            if constexpr (RES) {
-                                const auto sw = __builtin_amdgcn_permlane32_swap(r[h][k], r[h][2 + k], false, false);
-                                rq[0][k] = sw[0];
-                                rq[1][k] = sw[1];
-                            }
-                        }
-#pragma unroll
-                        for (int w = 0; w < 2; ++w) {
-                            if constexpr (!KEEP) affine(2 * h + w);
-#pragma unroll
-                            for (int k = 0; k < 2; ++k) {
-                                f32x2 v2;
-#pragma unroll
-                                for (int u = 0; u < 2; ++u) {
-                                    const int g = 2 * h + w;
-                                    float v = acc[b][c][4 * g + 2 * k + u] * sc[g][2 * k + u] + shf[g][2 * k + u];
-                                    if constexpr (RES)
-                                        v += TypeOps<T>::to_f(__builtin_bit_cast(T, (uint16_t)(u ? rq[w][k] >> 16 : rq[w][k] & 0xffffu)));
-                                    v2[u] = act_t<T, ACT>(v);
-                                }
-                                typedef T t2 __attribute__((ext_vector_type(2)));
-                                q[w][k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v2, t2));
-                            }
-                        }
-#pragma unroll
-                        for (int k = 0; k < 2; ++k) {
-                            const auto sw = __builtin_amdgcn_permlane32_swap(q[0][k], q[1][k], false, false);
-                            o[h][k] = sw[0];
-                            o[h][2 + k] = sw[1];
-                        }
-                    }
-                    exchange16(o[0], o[1]);
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) __builtin_amdgcn_raw_buffer_store_b128(o[h], ry, (int)off[h], 0, 0);
+                    const bool in = row_of(b, 16 * h + (lane & 15), row);
+                    off[h] = in & (n < Nc) ? (row + n) * 2u : kOutOfRange;
                 }
+                u32x4 o[2], r[2];
+                if constexpr (RES) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) r[h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, (int)off[h], 0, 0));
+                    exchange16(r[0], r[1]);
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {  // channels 16 h .. 16 h + 15 of the block, quarters 2 h and 2 h + 1
+                    uint32_t q[2][2], rq[2][2];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        if constexpr (RES) {
+                            const auto sw = __builtin_amdgcn_permlane32_swap(r[h][k], r[h][2 + k], false, false);
+                            rq[0][k] = sw[0];
+                            rq[1][k] = sw[1];
+                        }
+                    }
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        if constexpr (!KEEP) affine(2 * h + w);
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            f32x2 v2;
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) {
+                                const int g = 2 * h + w;
+                                float v = acc[b][c][4 * g + 2 * k + u] * sc[g][2 * k + u] + shf[g][2 * k + u];
+                                if constexpr (RES)
+                                    v += TypeOps<T>::to_f(__builtin_bit_cast(T, (uint16_t)(u ? rq[w][k] >> 16 : rq[w][k] & 0xffffu)));
+                                v2[u] = act_t<T, ACT>(v);
+                            }
+                            typedef T t2 __attribute__((ext_vector_type(2)));
+                            q[w][k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v2, t2));
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const auto sw = __builtin_amdgcn_permlane32_swap(q[0][k], q[1][k], false, false);
+                        o[h][k] = sw[0];
+                        o[h][2 + k] = sw[1];
+                    }
+                }
+                exchange16(o[0], o[1]);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) __builtin_amdgcn_raw_buffer_store_b128(o[h], ry, (int)off[h], 0, 0);
             }
         }
     };

@@ -63,3 +63,17 @@ def rel_err(g: np.ndarray, o: np.ndarray) -> float:
 
 def bits(t: torch.Tensor) -> bytes:
     return t.detach().cpu().contiguous().view(torch.uint8).numpy().tobytes()
+
+
+# The kernel behind an op of paths 2 and 3 shows in its LDS size alone (ElasticOp.info.lds_bytes).
+def patch_lds(tile_n, pixels):
+    """3x3 patch kernel: two buffers of 64-byte pixels, three stages of three taps, 28 bytes per channel."""
+    return 2 * pixels * 64 + 9 * tile_n * 64 + 28 * tile_n
+
+
+def pipe_lds(tile_m, tile_n):
+    """Register-tile pipeline: up to five stages of a 128-byte K chunk (in half a CU's LDS below 24 KiB a
+    stage), 28 bytes per column."""
+    stage = (tile_m + tile_n) * 128
+    room = (160 if stage >= 24 * 1024 else 80) * 1024 - 28 * tile_n
+    return min(5, room // stage) * stage + 28 * tile_n

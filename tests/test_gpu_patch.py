@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import bits, empty, f32_dev, gpu_available, ints, rand, rel_err, to_f64
+from gpu_util import bits, empty, f32_dev, gpu_available, ints, patch_lds, rand, rel_err, to_f64
 
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not gpu_available(), reason="needs an MI355X")]
@@ -34,7 +34,8 @@ def ops():
 
 def _is_patch(op, tile_n):
     from paper_2307_04339_amd import _lib as L
-    return (op.info.path, op.info.tile_m, op.info.tile_n, op.info.ksplit) == (L.PATH_DMA_UNIFORM, 256, tile_n, 1)
+    return ((op.info.path, op.info.tile_m, op.info.tile_n, op.info.ksplit) == (L.PATH_DMA_UNIFORM, 256, tile_n, 1)
+            and op.info.lds_bytes in (patch_lds(tile_n, 512), patch_lds(tile_n, 768)))
 
 
 @pytest.mark.parametrize("case", CASES)

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import bits, empty, f32_dev, gpu_available, rand, rel_err, to_f64
+from gpu_util import bits, empty, f32_dev, gpu_available, pipe_lds, rand, rel_err, to_f64
 
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not gpu_available(), reason="needs an MI355X")]
@@ -21,12 +21,9 @@ def ops():
 
 
 def _is_pipe(op, tile):
-    # no other kernel of this path has these LDS sizes: two or more stages plus 28 bytes per column
     from paper_2307_04339_amd import _lib as L
-    tm, tn = tile
     return (op.info.path in (L.PATH_DMA, L.PATH_DMA_UNIFORM)
-            and (op.info.tile_m, op.info.tile_n, op.info.ksplit) == (tm, tn, 1)
-            and (op.info.lds_bytes - 28 * tn) % ((tm + tn) * 128) == 0)
+            and (op.info.tile_m, op.info.tile_n, op.info.ksplit) == (*tile, 1) and op.info.lds_bytes == pipe_lds(*tile))
 
 
 def _elastic(op, y, orc):

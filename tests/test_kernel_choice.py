@@ -4,6 +4,7 @@ import ctypes
 
 import pytest
 
+from gpu_util import patch_lds, pipe_lds
 from paper_2307_04339_amd import _lib as L
 
 FAKE = 0x10000
@@ -24,10 +25,6 @@ def conv(n, h, w, c, k, ks, stride=1):
     return tile_of(kind=L.OP_CONV2D, dtype=L.F16, n=n, h=h, w=w, c=c, k=k, kh=ks, kw=ks, stride=stride, pad=ks // 2)
 
 
-# LDS of the patch kernel's forms: two buffers of pixels, nine taps of weights, 28 bytes per channel
-PATCH_LDS = [2 * pixels * 64 + 9 * tn * 64 + 28 * tn for pixels, tn in [(512, 64), (512, 128), (768, 64)]]
-
-
 # the patch kernel takes 256 pixels of one image where a tile over several would need too many padded ones
 @pytest.mark.parametrize("n,h,w,c,k,patch", [
     (128, 1, 1, 512, 512, False), (128, 4, 4, 512, 512, False), (64, 5, 5, 256, 256, False), (128, 1, 64, 256, 256, False),
@@ -37,13 +34,7 @@ PATCH_LDS = [2 * pixels * 64 + 9 * tn * 64 + 28 * tn for pixels, tn in [(512, 64
 ])
 def test_patch_kernel_needs_full_tiles(n, h, w, c, k, patch):
     tm, _, lds = conv(n, h, w, c, k, 3)
-    assert (tm == 256 and lds in PATCH_LDS) == patch
-
-
-def pipe_lds(tm, tn):
-    """LDS of the register-tile pipeline: up to five stages of a 128-byte K chunk, 28 bytes per column."""
-    stage = (tm + tn) * 128
-    return min(5, ((160 if stage >= 24 * 1024 else 80) * 1024 - 28 * tn) // stage) * stage + 28 * tn
+    assert (tm == 256 and lds in (patch_lds(64, 512), patch_lds(128, 512), patch_lds(64, 768))) == patch
 
 
 def is_pipe(tm, tn, lds):
