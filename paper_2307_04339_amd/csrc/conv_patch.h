@@ -31,8 +31,9 @@
 // What bounds it and what it measured (fp16, back to back in a captured graph, against the implicit
 // GEMM before): the MFMA rate of one wave per SIMD.  A step of 256x128 takes 0.97 us on the whole
 // chip (0.64 at the nominal clock, 0.73 without its LDS reads, 0.87 without its loads), so the
-// matrix cores are busy three quarters of the K loop; a launch adds about 8 us for the first loads,
-// the parameter decode and the last epilogue.  8x112x112x128->128 41.1 -> 33.6 us,
+// matrix cores are busy two thirds of the K loop; a launch adds about 8 us for the first loads,
+// the parameter decode and the last epilogue.  By the counters of 8x112x112x128->128 they are busy
+// half of a wave's life, and a wave waits for loads or LDS 27% of it.  8x112x112x128->128 41.1 -> 33.6 us,
 // 8x56x56x256->256 36.7 -> 30.0, 8x28x28x512->512 44.5 -> 32.1, 8x112x112x64->128 29.5 -> 24.0.
 // Issued in one run per k-step instead of one by one between the MFMAs, the operand reads and loads
 // cost 0.08 us a step.

@@ -144,7 +144,7 @@ __device__ __forceinline__ float act_c(float v) {
 // v / 2 (1 + erff(v / sqrt 2)), which it replaces and exceeds nowhere): [-9, -4] 3.9e-6 / 9e-7 (1), [-4, -2]
 // 9.4e-7 / 2.2e-7 (4.7e-4 / 6.7e-5), [-2, -1.25] 4.3e-7 / 9.9e-8 (1.2e-6 / 2.5e-7), [-1.25, -0.5] 2.8e-7 /
 // 6.2e-8 (4.8e-7 / 9.5e-8), [-0.5, 0.5] 1.4e-7 / 3.9e-8 (1.5e-7 / 4.0e-8), above 1.2e-7 / 3.7e-8 (1.4e-7 / 4.0e-8).
-// 4096 x 3072 x 768 with it and the rest of an encoder layer 202 us, 196 with a shorter form that lost bits.
+// An encoder layer of 8 x 512 tokens takes 202 us with it, 196 with a shorter form that lost bits.
 __device__ __forceinline__ float gelu_16(float v) {
     const float u = v * v, h = 0.5f * v, z = __builtin_fabsf(v);
     float p = __builtin_fmaf(-1.3304877e-05f, u, 0.00022072377f);

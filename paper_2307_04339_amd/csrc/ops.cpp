@@ -181,8 +181,8 @@ static int pipe_tile_n(int cfg) {
 // and 32-bit offsets per batch entry: CFG_PIPE_*, or 0 where igemm_dma_kernel stays, which would take
 // tile `other`.  The tile with the least estimated time: rounds of tiles over the CUs x (K chunks x the
 // chunk's time + the rest of a tile's), in ns, fitted to a sweep of products and convolutions (one
-// workgroup per CU; a 64x64 chunk takes 220 ns, a 256x192 one 1350 on the whole chip: the load path's
-// 33 bytes per clock and CU).  Measured back to back in a captured graph, bf16, igemm_dma_kernel -> this:
+// workgroup per CU, also for 64x64 tiles, of which two fit: they share the load path; a 64x64 chunk
+// takes 220 ns, a 256x192 one 1350 on the whole chip: the load path's 33 bytes per clock and CU).  Measured back to back in a captured graph, bf16, igemm_dma_kernel -> this:
 // 4096x2304x768 28.9 -> 23.3 us (256x192), 4096x768x3072 31.7 -> 26.3 (128x128), 2048x2304x768 20.7 ->
 // 16.2 (256x128), 2048x768x3072 22.0 -> 19.0 (128x64), 8x56x56x128->256 3x3/2 12.7 -> 10.9 (128x64),
 // 16x7x7x160->960 1x1 6.7 -> 4.8 (64x64).  [k][n] right operands (attention's P V, bf16, from the
