@@ -22,9 +22,9 @@
 //
 // What bounds it: the load path.  128x128 chunks of a K = 3072 product arrive at 34 bytes per clock and
 // CU, 0.42 us a chunk on 0.21 us of MFMA; wider tiles need fewer bytes per flop but leave CUs idle on
-// small products (the tile rule and its times are in ops.cpp).  By the counters of that product the
-// matrix cores are busy 44% of a wave's life, which waits for loads or LDS 37% of it.  8192x4096x1024 bf16 takes 77 us, 0.90
-// PFLOP/s, against 88 before; 4096x768x3072 26 against 32.
+// small products (the tile rule and its times are in ops.cpp).  By the counters of 4096x768x3072 the matrix
+// cores are busy 44% of a wave's life, which waits for loads or LDS 37% of it.  That product takes 26 us
+// (igemm_dma_kernel 32), 8192x4096x1024 bf16 77 us, 0.90 PFLOP/s (88).
 //
 // K order per output element (fixed, whatever the elastic configuration): chunks in order, k-steps
 // in order.
